@@ -798,25 +798,32 @@ __global__ void inject_kernel(const double* __restrict__ Gbar, const double* __r
   inj[((int64_t)q * (K + 1) + n) * 4 * npos + x] = acc;
 }
 
-// Gbar = dt (G - Gm); J (+)= 1/2 dt sum (G - Gm)^2 over n entries (one block,
-// fixed reduction order; accumulate adds to J, for the chunks after the first)
+// Gbar = dt (G - Gm); J (+)= 1/2 dt sum (G - Gm)^2 over nq sources of n
+// entries each (one block, fixed reduction order; accumulate adds to J, for
+// the chunks after the first).  Each source is reduced by itself and added in
+// turn, so J does not depend on how the sources are cut into chunks.
 __global__ __launch_bounds__(1024) void misfit_kernel(const double* __restrict__ G, const double* __restrict__ Gm,
-                                                      double* __restrict__ Gbar, double* __restrict__ J, int64_t n,
-                                                      double dt, int accumulate) {
+                                                      double* __restrict__ Gbar, double* __restrict__ J, int nq,
+                                                      int64_t n, double dt, int accumulate) {
   __shared__ double red[1024];
-  double acc = 0.0;
-  for (int64_t t = threadIdx.x; t < n; t += 1024) {
-    const double r = G[t] - Gm[t];
-    Gbar[t] = dt * r;
-    acc += r * r;
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+  double j = accumulate ? *J : 0.0;
+  for (int q = 0; q < nq; ++q) {
+    double acc = 0.0;
+    for (int64_t t = (int64_t)q * n + threadIdx.x; t < (q + 1) * n; t += 1024) {
+      const double r = G[t] - Gm[t];
+      Gbar[t] = dt * r;
+      acc += r * r;
+    }
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int w = 512; w > 0; w >>= 1) {
+      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) j += 0.5 * dt * red[0];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *J = (accumulate ? *J : 0.0) + 0.5 * dt * red[0];
+  if (threadIdx.x == 0) *J = j;
 }
 
 // src[q][k][bp] = sum_jd det_sp[jd][bp] r(q, jd, K - k), k = 0..K, with
@@ -963,7 +970,7 @@ hipError_t launch_misfit(const Plan& p, const double* G, const double* Gm, doubl
                          hipStream_t s) {
   const int64_t off = p.cq0 * p.Nd * (int64_t)K;
   hipLaunchKernelGGL(misfit_kernel, dim3(1), dim3(1024), 0, s, G + off, Gm + off, Gbar + off, J,
-                     p.cnq * p.Nd * (int64_t)K, p.prob.dt, p.cq0 > 0 ? 1 : 0);
+                     (int)p.cnq, p.Nd * (int64_t)K, p.prob.dt, p.cq0 > 0 ? 1 : 0);
   return hipGetLastError();
 }
 
