@@ -316,23 +316,18 @@ int rte_batch_gradient(rte_batch* batch, const void* const* mu_a, const void* co
                        double* const* dmu_s, double* const* G, void* const* workspaces,
                        const int64_t* workspace_bytes, void* stream);
 
-/* Launch schedule of the per-step kernels.  The units-per-wave and
+/* Launch schedule of the per-step kernels.  The line kernel has one variant
+ * per extended length, so line_units_per_wave, line_waves_per_unit and
+ * line_global_tables are checked and kept but change nothing; the
  * tiles-per-block choices compute the same result bit for bit; the generic
  * line kernel computes the same operator with another FFT factorisation
- * (equal to rounding).  Zero fields mean the default (one unit per
- * workgroup, two waves per unit, tables staged unless set, the node tiling
- * of the plan).  The waves-per-unit and table-placement choices are bitwise
- * neutral as well.  Extended lengths outside {90, 160, 288, 540} have one
- * four-step variant (one unit, two waves, global tables) whatever is set.
- *   line_units_per_wave : 1 or 2 work units (two lines x four slots of one
- *                         ordinate group) per workgroup of the four-step line
- *                         kernel, transformed one after the other
- *   line_waves_per_unit : 1 or 2 waves sharing the transforms of one unit
- *   line_global_tables  : 1 = the FFT twiddles and derivative multipliers are
- *                         read from global memory (cached) instead of being
- *                         staged in LDS (smaller LDS footprint)
+ * (equal to rounding).  Zero fields mean the default (one unit, two waves, 0,
+ * the node tiling of the plan).
+ *   line_units_per_wave : 1 or 2
+ *   line_waves_per_unit : 1 or 2
+ *   line_global_tables  : 0 or 1
  *   line_generic        : 1 = use the generic Stockham line kernel even where
- *                         the extended length has a four-step split
+ *                         the extended length has a split
  *   node_tiles_per_block: 16-node tiles per workgroup of the node passes
  *                         (1, 2 or 4; times the 16-slot row tiles, at most 8
  *                         waves; plans with M > 64 always use 1)          */

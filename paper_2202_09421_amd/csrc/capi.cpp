@@ -777,49 +777,14 @@ int autotune(Plan& p, const void* mu_a, const void* mu_s, void* wsp, int64_t wsb
   const rte_schedule start = p.sched;
   rte_schedule best = p.sched;
 
-  // line passes: forward and transpose launches of each admissible variant
-  struct LineCand {
-    int upw, nw, generic, tg;
-  };
-  std::vector<LineCand> line_cands;
-  const bool four = p.fcx.n1 > 0 || p.fcy.n1 > 0;
-  if (four)
-    for (int upw : {2, 1})
-      for (int nw : {1, 2})
-        for (int tg : {0, 1}) line_cands.push_back({upw, nw, 0, tg});
-  // the generic kernel transforms two ordinates of one line as one complex
-  // line (less accurate near beams): a candidate only without a split
-  if (!four) line_cands.push_back({1, 1, 1, 0});
-  double best_ms = 1e30;
-  for (const auto& c : line_cands) {
-    p.sched.line_units_per_wave = c.upw;
-    p.sched.line_waves_per_unit = c.nw;
-    p.sched.line_generic = c.generic;
-    p.sched.line_global_tables = c.tg;
-    double f = 0.0, b = 0.0;
-    const LineLaunch lf = tset.lf, lb = tset.lb;
-    int rc = time_graph(p, st, reps, [&](hipStream_t s, int) { return launch_lines(p, lf, s); }, &f);
-    if (rc == RTE_OK) rc = time_graph(p, st, reps, [&](hipStream_t s, int) { return launch_lines(p, lb, s); }, &b);
-    if (rc != RTE_OK) {
-      p.sched = start;
-      p.prof = prof;
-      return rc;
-    }
-    if (f + b < best_ms) {
-      best_ms = f + b;
-      best.line_units_per_wave = c.upw;
-      best.line_waves_per_unit = c.nw;
-      best.line_generic = c.generic;
-      best.line_global_tables = c.tg;
-    }
-  }
-  p.sched.line_units_per_wave = best.line_units_per_wave;
-  p.sched.line_waves_per_unit = best.line_waves_per_unit;
+  // line passes: one variant per extended length.  The generic kernel (which
+  // transforms two ordinates of one line as one complex line, less accurate
+  // near beams) only where neither direction has a split.
+  best.line_generic = (p.fcx.n1 > 0 || p.fcy.n1 > 0) ? 0 : 1;
   p.sched.line_generic = best.line_generic;
-  p.sched.line_global_tables = best.line_global_tables;
 
   // node passes: tiles per block
-  best_ms = 1e30;
+  double best_ms = 1e30;
   for (int nt : {1, 2, 4}) {
     if (!node_tiles_ok(p, nt)) continue;
     p.sched.node_tiles_per_block = nt;

@@ -1,8 +1,11 @@
 // Compile-time FFT codelets held entirely in registers.
 //
 // dft<N, S>(x) replaces x[0..N) by sum_n x[n] exp(S 2 pi i n k / N) (S = -1
-// forward, +1 inverse, unnormalised) for N a product of 2, 3, 4, 5.  Mixed
-// radix decimation in time: N = P Q, Q-point transforms of the P decimated
+// forward, +1 inverse, unnormalised) for N a product of 2, 3, 4, 5.  N = P Q
+// with P the power of the smallest prime of N where that leaves coprime
+// factors: the prime-factor index maps (Good 1958), n -> (n mod P, n mod Q)
+// and k = Q k1 + P k2 mod N, need no twiddles.  A prime power is split by
+// mixed radix decimation in time: Q-point transforms of the P decimated
 // subsequences, twiddles exp(S 2 pi i p k2 / N), then P-point transforms
 // across p.  Every index is a compile-time constant after unrolling, so the
 // whole transform lives in registers.  Twiddle constants come from a
@@ -82,6 +85,24 @@ constexpr int first_radix(int N) {
   return (N % 4 == 0 && N != 4) ? 4 : (N % 2 == 0 && N != 2) ? 2 : (N % 3 == 0 && N != 3) ? 3 : (N % 5 == 0 && N != 5) ? 5 : N;
 }
 
+// largest power of the smallest prime factor of N (2, 3 or 5) that divides N
+constexpr int prime_part(int N) {
+  const int p = N % 2 == 0 ? 2 : (N % 3 == 0 ? 3 : 5);
+  int q = 1;
+  while (N % p == 0) {
+    N /= p;
+    q *= p;
+  }
+  return q;
+}
+
+// the n in [0, P Q) with n mod P = a and n mod Q = b (P, Q coprime)
+constexpr int crt(int P, int Q, int a, int b) {
+  int n = b;
+  while (n % P != a) n += Q;
+  return n;
+}
+
 }  // namespace ct
 
 template <typename T>
@@ -99,6 +120,17 @@ RTE_HD cx<T> cx_si(cx<T> a) { return S > 0 ? cx<T>{-a.im, a.re} : cx<T>{a.im, -a
 template <typename T>
 RTE_HD cx<T> cx_rot(cx<T> a, double c, double s) {
   return {a.re * T(c) - a.im * T(s), a.re * T(s) + a.im * T(c)};
+}
+
+// x * exp(S 2 pi i e / N), 0 <= e < N a constant after unrolling; quarter
+// turns without arithmetic (a product with an exact zero is not folded)
+template <int N, int S, typename T>
+RTE_HD cx<T> cx_tw(cx<T> a, int e) {
+  if (e == 0) return a;
+  if (4 * e == N) return cx_si<S>(a);
+  if (2 * e == N) return {-a.re, -a.im};
+  if (4 * e == 3 * N) return cx_si<-S>(a);
+  return cx_rot(a, ct::roots<N>.c[e], S * ct::roots<N>.s[e]);
 }
 
 template <int N, int S, typename T>
@@ -167,30 +199,50 @@ struct Dft<5, S, T> {
 
 template <int N, int S, typename T>
 struct Dft {
-  static constexpr int P = ct::first_radix(N);
+  static constexpr bool PF = ct::prime_part(N) != N;
+  static constexpr int P = PF ? ct::prime_part(N) : ct::first_radix(N);
   static constexpr int Q = N / P;
   static RTE_HD void run(cx<T>* x) {
     cx<T> y[N];
+    if constexpr (PF) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      cx<T> t[Q];
+      for (int a = 0; a < P; ++a) {
+        cx<T> t[Q];
 #pragma unroll
-      for (int q = 0; q < Q; ++q) t[q] = x[p + P * q];
-      Dft<Q, S, T>::run(t);
+        for (int b = 0; b < Q; ++b) t[b] = x[ct::crt(P, Q, a, b)];
+        Dft<Q, S, T>::run(t);
+#pragma unroll
+        for (int k2 = 0; k2 < Q; ++k2) y[a * Q + k2] = t[k2];
+      }
 #pragma unroll
       for (int k2 = 0; k2 < Q; ++k2) {
-        const int e = (p * k2) % N;
-        y[p * Q + k2] = (e == 0) ? t[k2] : cx_rot(t[k2], ct::roots<N>.c[e], S * ct::roots<N>.s[e]);
+        cx<T> t[P];
+#pragma unroll
+        for (int a = 0; a < P; ++a) t[a] = y[a * Q + k2];
+        Dft<P, S, T>::run(t);
+#pragma unroll
+        for (int k1 = 0; k1 < P; ++k1) x[(Q * k1 + P * k2) % N] = t[k1];
       }
-    }
+    } else {
 #pragma unroll
-    for (int k2 = 0; k2 < Q; ++k2) {
-      cx<T> t[P];
+      for (int p = 0; p < P; ++p) {
+        cx<T> t[Q];
 #pragma unroll
-      for (int p = 0; p < P; ++p) t[p] = y[p * Q + k2];
-      Dft<P, S, T>::run(t);
+        for (int q = 0; q < Q; ++q) t[q] = x[p + P * q];
+        Dft<Q, S, T>::run(t);
 #pragma unroll
-      for (int k1 = 0; k1 < P; ++k1) x[k2 + Q * k1] = t[k1];
+        for (int k2 = 0; k2 < Q; ++k2)
+          y[p * Q + k2] = cx_tw<N, S>(t[k2], (p * k2) % N);
+      }
+#pragma unroll
+      for (int k2 = 0; k2 < Q; ++k2) {
+        cx<T> t[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) t[p] = y[p * Q + k2];
+        Dft<P, S, T>::run(t);
+#pragma unroll
+        for (int k1 = 0; k1 < P; ++k1) x[k2 + Q * k1] = t[k1];
+      }
     }
   }
 };

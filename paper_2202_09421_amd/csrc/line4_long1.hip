@@ -1,28 +1,26 @@
-// Four-step line passes for extended lengths 900..1200 (900, 960, 972, 1000, 1024, 1080, 1152, 1200).
-// Each length above 600 up to 1200 that splits into two factors of at most
-// 40 is instantiated once (1125 = 3^2 5^3 has no such split and uses the
-// generic kernel): one unit per two-wave workgroup, every table read from
-// global memory.
+// Line passes for extended lengths 900, 960, 972, 1000, 1024, 1080, 1152, 1200,
+// 1125.
 #include "line4_impl.h"
 
 namespace rte {
 
 template <typename T>
-static hipError_t longs(const Lines4Args<T>& a, bool adj, hipStream_t s) {
-  switch (a.fc.Np) {
-    case 900: return adj ? go_long<T, true, 30, 30>(a, s) : go_long<T, false, 30, 30>(a, s);
-    case 960: return adj ? go_long<T, true, 32, 30>(a, s) : go_long<T, false, 32, 30>(a, s);
-    case 972: return adj ? go_long<T, true, 27, 36>(a, s) : go_long<T, false, 27, 36>(a, s);
-    case 1000: return adj ? go_long<T, true, 25, 40>(a, s) : go_long<T, false, 25, 40>(a, s);
-    case 1024: return adj ? go_long<T, true, 32, 32>(a, s) : go_long<T, false, 32, 32>(a, s);
-    case 1080: return adj ? go_long<T, true, 30, 36>(a, s) : go_long<T, false, 30, 36>(a, s);
-    case 1152: return adj ? go_long<T, true, 32, 36>(a, s) : go_long<T, false, 32, 36>(a, s);
-    case 1200: return adj ? go_long<T, true, 30, 40>(a, s) : go_long<T, false, 30, 40>(a, s);
+static hipError_t longs(const Lines4Args<T>& a, int Np, int nq, bool adj, hipStream_t s) {
+  switch (Np) {
+    case 900: return adj ? go_one<T, true, 4, 225>(a, nq, s) : go_one<T, false, 4, 225>(a, nq, s);
+    case 960: return adj ? go_one<T, true, 15, 64>(a, nq, s) : go_one<T, false, 15, 64>(a, nq, s);
+    case 972: return adj ? go_one<T, true, 18, 54>(a, nq, s) : go_one<T, false, 18, 54>(a, nq, s);
+    case 1000: return adj ? go_one<T, true, 10, 100>(a, nq, s) : go_one<T, false, 10, 100>(a, nq, s);
+    case 1024: return adj ? go_one<T, true, 16, 64>(a, nq, s) : go_one<T, false, 16, 64>(a, nq, s);
+    case 1080: return adj ? go_one<T, true, 10, 108>(a, nq, s) : go_one<T, false, 10, 108>(a, nq, s);
+    case 1152: return adj ? go_one<T, true, 18, 64>(a, nq, s) : go_one<T, false, 18, 64>(a, nq, s);
+    case 1200: return adj ? go_one<T, true, 8, 150>(a, nq, s) : go_one<T, false, 8, 150>(a, nq, s);
+    case 1125: return adj ? go_one<T, true, 15, 75>(a, nq, s) : go_one<T, false, 15, 75>(a, nq, s);
     default: return hipErrorNotSupported;
   }
 }
 
-hipError_t lines4_long1(const Lines4Args<double>& a, bool adj, hipStream_t s) { return longs(a, adj, s); }
-hipError_t lines4_long1(const Lines4Args<float>& a, bool adj, hipStream_t s) { return longs(a, adj, s); }
+hipError_t lines4_long1(const Lines4Args<double>& a, int Np, int nq, bool adj, hipStream_t s) { return longs(a, Np, nq, adj, s); }
+hipError_t lines4_long1(const Lines4Args<float>& a, int Np, int nq, bool adj, hipStream_t s) { return longs(a, Np, nq, adj, s); }
 
 }  // namespace rte

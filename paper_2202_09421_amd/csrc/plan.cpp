@@ -153,13 +153,6 @@ static bool build_fc(const rte_problem& pb, int n, double h, std::vector<double>
   for (int i = 0; i < d * d; ++i) buf.push_back(pb.fc_Q[i]);
   offs.push_back(buf.size());
   for (int i = 0; i < C * d; ++i) buf.push_back(pb.fc_A[i]);
-  // roots of unity for the four-step kernel
-  offs.push_back(buf.size());
-  for (int e = 0; e < Np; ++e) {
-    const double ang = -2.0 * kPi * (double)e / (double)Np;
-    buf.push_back(std::cos(ang));
-    buf.push_back(std::sin(ang));
-  }
   // continuation matrix (Sec. 4.3 steps 1-4 as one linear map): extension
   // value p (0 <= p < C + E) = sum_k MR[p][k] g[n-d+k] + sum_k ML[p][k] g[d-1-k]
   // with MR[p][k] = sum_j A[p][j] Q[k][j] (p < C) and
@@ -176,6 +169,26 @@ static bool build_fc(const rte_problem& pb, int n, double h, std::vector<double>
           for (int j = 0; j < d; ++j) acc += (long double)pb.fc_A[row * d + j] * (long double)pb.fc_Q[k * d + j];
         buf.push_back((double)acc);
       }
+  }
+  // the four-step kernel's copies: the matrix transposed (its lanes read
+  // consecutive rows; each side padded to kMaxFcD rows), the multipliers in the order of its last stage
+  const size_t mx0 = offs.back(), mu0 = offs[1];
+  offs.push_back(buf.size());
+  for (int k = 0; k < 2 * kMaxFcD; ++k)
+    for (int p = 0; p < CE; ++p) {
+      const int row = k % kMaxFcD;
+      buf.push_back(row < d ? buf[mx0 + (size_t)p * 2 * d + (k / kMaxFcD) * d + row] : 0.0);
+    }
+  std::vector<int> mu_order, tw_order;
+  line4_orders(Np, mu_order, tw_order);
+  offs.push_back(buf.size());
+  for (int k : mu_order) buf.push_back(buf[mu0 + k]);
+  if (buf.size() % 2) buf.push_back(0.0);   // 16-byte aligned twiddles
+  offs.push_back(buf.size());
+  for (int e : tw_order) {
+    const double ang = -2.0 * kPi * (double)e / (double)Np;
+    buf.push_back(std::cos(ang));
+    buf.push_back(std::sin(ang));
   }
   // the extension values are formed by one thread each (CE <= 64); the
   // transpose keeps its 2d fold values in the C+E extension positions
@@ -328,6 +341,7 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   p.cq0 = 0;
   p.cnq = p.chunk;
   p.stream_nt = p.chunk * p.inst_stride * (prob->dtype == RTE_F64 ? 8 : 4) > kStreamNtBytes;
+  p.line_nt = p.chunk * p.inst_stride * (prob->dtype == RTE_F64 ? 8 : 4) > kLineNtBytes;
   const int M = (int)p.M;
   const double dx = (prob->xmax - prob->xmin) / prob->Nx;
   const double dy = (prob->ymax - prob->ymin) / prob->Ny;
@@ -521,9 +535,6 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   }
 
   p.sched.node_tiles_per_block = node_tiles_default(p);
-  p.fc_same = p.fcx.n == p.fcy.n && p.fcx.Np == p.fcy.Np && p.fcx.E == p.fcy.E &&
-              std::equal(fcbuf.begin() + ox[1], fcbuf.begin() + ox[2], fcbuf.begin() + oy[1]);
-
   // ---- upload
   std::vector<int32_t> slotm(p.slot_m.begin(), p.slot_m.end());
   bool ok = upload(xi, &p.dev.xi) && upload(eta, &p.dev.eta) && upload(Wt, &p.dev.Wt) && upload(bc, &p.dev.bc) &&
@@ -539,10 +550,18 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
     return RTE_EDEVICE;
   }
   const double* fb = p.dev.fc_buf;
-  p.fcx.tw = fb + ox[0]; p.fcx.mu = fb + ox[1]; p.fcx.Q = fb + ox[2]; p.fcx.A = fb + ox[3]; p.fcx.roots = fb + ox[4];
-  p.fcy.tw = fb + oy[0]; p.fcy.mu = fb + oy[1]; p.fcy.Q = fb + oy[2]; p.fcy.A = fb + oy[3]; p.fcy.roots = fb + oy[4];
-  p.fcx.Mx = fb + ox[5];
-  p.fcy.Mx = fb + oy[5];
+  for (int k = 0; k < 2; ++k) {
+    FcPlanDev& fc = k ? p.fcy : p.fcx;
+    const std::vector<size_t>& o = k ? oy : ox;
+    fc.tw = fb + o[0];
+    fc.mu = fb + o[1];
+    fc.Q = fb + o[2];
+    fc.A = fb + o[3];
+    fc.Mx = fb + o[4];
+    fc.MxT = fb + o[5];
+    fc.mup = fb + o[6];
+    fc.tw4 = fb + o[7];
+  }
   *out = reinterpret_cast<rte_plan*>(P);
   return RTE_OK;
 }

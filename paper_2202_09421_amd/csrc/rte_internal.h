@@ -19,9 +19,12 @@ constexpr int kMaxFcD = 8;       // matching points supported
 // the 256 MiB memory-side cache that holds smaller plans' arrays between
 // launches
 constexpr int64_t kStreamNtBytes = int64_t(64) << 20;
+// the line passes' output stores take the hint from a much smaller size on
+// (gradient steps on 129 x 129 x 16 with two sources, 4.3 MB per array: 5 %
+// faster; 257 x 257 x 32: 0.5 %; 65 x 65 x 16, 0.6 MB, which the next node
+// pass still finds in L2: 4 % slower)
+constexpr int64_t kLineNtBytes = int64_t(2) << 20;
 constexpr int kLineThreads = 128; // generic (Stockham) line kernel
-constexpr int kFcTab = 384;      // continuation matrix entries ((C+E) * 2d) staged by the four-step kernel
-constexpr int kLongLine = 600;   // four-step lengths above this read the continuation matrix from global memory
 
 void set_error(const std::string& msg);
 const char* last_error();
@@ -43,12 +46,18 @@ struct FcPlanDev {
   const double* Q;          // d*d
   const double* A;          // C*d
   int n1, n2;               // four-step split Np = n1 * n2 (0: generic Stockham kernel)
-  const double* roots;      // Np complex roots exp(-2 pi i e / Np), interleaved
   const double* Mx;         // (C+E) x 2d continuation matrix [MR | ML] (four-step kernel)
+  const double* MxT;        // its transpose, [side][kMaxFcD][C+E] (zero beyond d)
+  const double* mup;        // mu in the order of the four-step kernel's last stage
+  const double* tw4;        // twiddles of the four-step kernel in job order, interleaved (re, im)
 };
 
 // Four-step splits with register codelets (Np -> n1 x n2); 0 if none.
 bool fourstep_split(int Np, int* n1, int* n2);
+// tables of the four-step kernel, empty if Np has no split: entry e of its
+// multipliers is mu[order] of frequency mu[e], and entry e of its twiddles is
+// exp(-2 pi i tw[e] / Np)
+void line4_orders(int Np, std::vector<int>& mu, std::vector<int>& tw);
 
 // Per-slot boundary rule for one node type (9 types: interior, 4 edges, 4 corners).
 struct BcRule {
@@ -99,7 +108,6 @@ struct Plan {
   int64_t nxp = 0;
   int64_t grp_stride = 0;   // ny * nxp * kGroup elements
   int64_t inst_stride = 0;  // G * grp_stride
-  bool fc_same = false;     // x and y FC plans identical: both line sets in one launch
   rte_schedule sched{1, 0, 0, 2, 1, 0};  // launch schedule (node_tiles_per_block resolved at create)
   int64_t sched_version = 0;       // bumped by every schedule change (graph keys)
   int64_t nb = 0;     // boundary nodes 2(nx+ny)-4
@@ -115,6 +123,7 @@ struct Plan {
   // one state array of a chunk exceeds kStreamNtBytes: the per-step kernels
   // stream their state arrays with the non-temporal hint (set at create)
   bool stream_nt = false;
+  bool line_nt = false;        // the same for the line passes' stores (kLineNtBytes)
   int64_t saved_chunk = -1;    // chunk whose forward states are in the workspace
   bool have_forward = false;   // a saved forward lives in the workspace
   int64_t saved_K = 0;
