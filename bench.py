@@ -46,7 +46,7 @@ WORD = {"f64": 8, "f32": 4}
 KERNEL_WORDS = {
     "lines_fwd": 4,    # x and y lines: read u twice, write -xi Dx u and -eta Dy u
     "node_fwd": 8,     # read u, X, Y, L^{n-1..n-3}; write u^{n+1}, L^n
-    "node_adj": 10,    # read atx, aty, P1^{n+1}, v^{n+2..n+4}, u^n; write v^{n+1}, w^n, P1^n
+    "node_adj": 9,     # read w^n, its two transposes, v^{n+1..n+3}, u^n; write v^n, w^{n-1}
     "lines_adj": 4,    # x and y lines: read w twice, write Dx^T(xi w) and Dy^T(eta w)
 }
 PATH_WORDS_STORE_ALL = 12  # algorithmic fwd + adj per unit: 6 + 6 words

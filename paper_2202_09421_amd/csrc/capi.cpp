@@ -91,29 +91,30 @@ int fwd_step(Ctx& c, int n, const void* un, void* unp1, double* flux) {
   return RTE_OK;
 }
 
-// One adjoint step n (K..1) given u^n: node pass (forms v^{n+1} from the
-// carried pieces of ubar^{n+1}, then w^n, P1^n and the gradient terms), then
-// the transposed line derivatives of w^n, carried to step n-1.
+// One adjoint step n (K..1) given u^n: node pass (v^n, the gradient terms of
+// step n and w^{n-1}), then the transposed line derivatives of w^{n-1}, which
+// step n - 1 reads (none follows step 1).
 int adj_step(Ctx& c, int n, const void* un) {
   NodeAdjLaunch na;
   na.atx = c.ws.atx;
   na.aty = c.ws.aty;
-  na.ap1 = c.ws.ap1;
-  na.v1_out = c.ws.vring[(n + 1) % 4];
+  na.w = c.ws.wbuf;
+  na.v_out = c.ws.vring[n % 4];
+  na.v1 = c.ws.vring[(n + 1) % 4];
   na.v2 = c.ws.vring[(n + 2) % 4];
   na.v3 = c.ws.vring[(n + 3) % 4];
-  na.v4 = c.ws.vring[n % 4];
   na.u = un;
   na.mu_a = c.mu_a;
   na.mu_s = c.mu_s;
   na.inj = c.ws.flux;
-  na.w_out = c.ws.wbuf;
   na.ga = c.ws.ga;
   na.gb = c.ws.gb;
   na.step = n;
   TIMED(RTE_K_NODE_ADJ, launch_node_adj(c.p, na, c.st));
-  LineLaunch ll{c.ws.wbuf, c.ws.atx, c.ws.aty, LINE_ADJ, 3};
-  TIMED(RTE_K_LINES_ADJ, launch_lines(c.p, ll, c.st));
+  if (n > 1) {
+    LineLaunch ll{c.ws.wbuf, c.ws.atx, c.ws.aty, LINE_ADJ, 3};
+    TIMED(RTE_K_LINES_ADJ, launch_lines(c.p, ll, c.st));
+  }
   return RTE_OK;
 }
 
@@ -194,13 +195,13 @@ int forward_chunk(Ctx& c, bool save, void* u_final) {
 }
 
 // Adjoint of the current chunk in pieces: start (zero ring and carries:
-// ubar^{K+1} = 0, v^{K+2..K+4} = 0), the restore of checkpoint j at the start
+// w^K = 0, v^{K+1..K+3} = 0), the restore of checkpoint j at the start
 // of segment j (checkpoint mode), and step n given u^n.
 int adjoint_start(Ctx& c) {
   for (int k = 0; k < 4; ++k) RTE_CHECK(launch_zero(c.ws.vring[k], c.S, c.st));
   RTE_CHECK(launch_zero(c.ws.atx, c.S, c.st));
   RTE_CHECK(launch_zero(c.ws.aty, c.S, c.st));
-  RTE_CHECK(launch_zero(c.ws.ap1, c.S, c.st));
+  RTE_CHECK(launch_zero(c.ws.wbuf, c.S, c.st));
   return RTE_OK;
 }
 
@@ -341,8 +342,8 @@ struct PsiArrays {
 };
 
 PsiArrays psi_arrays(const Plan& p, const Workspace& ws) {
-  if (p.ckpt_every == 0) return {{ws.vring[3], ws.ap1}, {ws.lring[0], ws.lring[1], ws.lring[2]}, ws.tx, ws.ty};
-  return {{ws.vring[0], ws.vring[1]}, {ws.vring[2], ws.vring[3], ws.ap1}, ws.atx, ws.aty};
+  if (p.ckpt_every == 0) return {{ws.vring[3], ws.wbuf}, {ws.lring[0], ws.lring[1], ws.lring[2]}, ws.tx, ws.ty};
+  return {{ws.vring[0], ws.vring[1]}, {ws.vring[2], ws.vring[3], ws.wbuf}, ws.atx, ws.aty};
 }
 
 // psi^k -> psi^{k+1}; upair = u^{K-k} (the forward state at the physical time of psi^k)
@@ -696,7 +697,7 @@ int tune_setup(Plan& p, const void* mu_a, const void* mu_s, void* wsp, int64_t w
   void* u0 = ws.states;
   void* u1 = static_cast<char*>(ws.states) + S;
   void* arrays[] = {ws.lring[0], ws.lring[1], ws.lring[2], ws.tx, ws.ty, ws.vring[0], ws.vring[1],
-                    ws.vring[2], ws.vring[3], ws.atx, ws.aty, ws.ap1};
+                    ws.vring[2], ws.vring[3], ws.atx, ws.aty, ws.wbuf};
   for (void* a : arrays) RTE_CHECK(launch_zero(a, S, st));
   RTE_CHECK(launch_zero(ws.flux, p.Nq * (p.K + 1) * 4 * p.npos * 8, st));
   RTE_CHECK(launch_zero(ws.ga, p.Nq * p.nx * p.ny * 8, st));
@@ -704,8 +705,8 @@ int tune_setup(Plan& p, const void* mu_a, const void* mu_s, void* wsp, int64_t w
   t->lf = LineLaunch{u0, ws.tx, ws.ty, LINE_FWD, 3};
   t->lb = LineLaunch{ws.wbuf, ws.atx, ws.aty, LINE_ADJ, 3};
   t->nf = NodeFwdLaunch{u0, ws.tx, ws.ty, ws.lring[1], ws.lring[2], ws.lring[0], mu_a, mu_s, u1, ws.lring[0], ws.flux, 0};
-  t->na = NodeAdjLaunch{ws.atx, ws.aty, ws.ap1, ws.vring[1], ws.vring[2], ws.vring[3], ws.vring[0], u0,
-                        mu_a, mu_s, ws.flux, ws.wbuf, ws.ga, ws.gb, (int)p.K};
+  t->na = NodeAdjLaunch{ws.atx, ws.aty, ws.wbuf, ws.vring[0], ws.vring[1], ws.vring[2], ws.vring[3], u0,
+                        mu_a, mu_s, ws.flux, ws.ga, ws.gb, (int)p.K};
   return RTE_OK;
 }
 

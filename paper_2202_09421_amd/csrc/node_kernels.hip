@@ -11,13 +11,17 @@
 //             entries (eq. RTE, last line), u~ elsewhere
 //   flux[w][pos] = sum_m kappa_w(m) u^{n+1}_m on boundary nodes (eq. OpMed)
 //
-// Adjoint node pass (exact transpose, reverse time): with v^k = P^T ubar^k,
-//   ubar^{n+1} = P1^{n+1} - c dt (Dx^T(xi w^{n+1}) + Dy^T(eta w^{n+1}))
-//   v^{n+1} = P^T ubar^{n+1}
-//   w^n  = sum_l chi_l v^{n+1+l}
-//   P1^n = v^{n+1} + c dt (b W w - (a + b) w) + D_e^T Gbar^n
-//   dJ/da += -c dt sum_m u^n_m w_m,   dJ/db += c dt sum_m u^n_m ((W w)_m - w_m)
-// The line passes of the same step then form the transposed derivatives of w^n.
+// Adjoint node pass (exact transpose, reverse time), step n: with w^n, the
+// transposed line derivatives of it and v^k = P^T ubar^k,
+//   P1^n = v^{n+1} + c dt (b W w^n - (a + b) w^n) + D_e^T Gbar^n
+//   ubar^n = P1^n - c dt (Dx^T(xi w^n) + Dy^T(eta w^n)),   v^n = P^T ubar^n
+//   dJ/da += -c dt sum_m u^n_m w^n_m,   dJ/db += c dt sum_m u^n_m ((W w^n)_m - w^n_m)
+//   w^{n-1} = chi0 v^n + chi1 v^{n+1} + chi2 v^{n+2} + chi3 v^{n+3}
+// The line passes then form the transposed derivatives of w^{n-1}.  A step cut
+// here (before the contraction of w^n and not after it) carries w, which the
+// line passes need in memory anyway, and not P1: 9 words per node and ordinate
+// instead of 10 (513 x 513 x 64, four sources: 978 us a launch against 1086 in
+// FP64, 521 against 624 in FP32, both at 4.5 to 5 TB/s).
 #include <algorithm>
 #include <type_traits>
 
@@ -470,17 +474,18 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_fwd_kernel(NodeFwd
 // ---------------------------------------------------------------- adjoint
 template <typename T>
 struct NodeAdjArgs {
-  const T* atx; const T* aty; T* ap1; T* v1_out;
-  const T* v2; const T* v3; const T* v4; const T* u;
+  const T* atx; const T* aty; T* w; T* v_out;
+  const T* v1; const T* v2; const T* v3; const T* u;
   const T* mu_a; const T* mu_s; const double* inj;
-  T* w_out; double* ga; double* gb;
+  double* ga; double* gb;
   const double* Wt; const BcRuleT* bct; const double* kappa;
   NodeGeom geo;
   int step;
   double cdt;
 };
 
-// ap1 is read (P1^{n+1}) and overwritten (P1^n) element by element by one lane.
+// w is read (w^n) and overwritten (w^{n-1}) element by element by one lane.
+// v1, v2, v3 = v^{n+1}, v^{n+2}, v^{n+3}.
 template <typename T, int RTC, bool NT>
 __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_adj_kernel(NodeAdjArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -494,32 +499,32 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_adj_kernel(NodeAdj
 
   const T* txq = a.atx + ib;
   const T* tyq = a.aty + ib;
-  T* p1q = a.ap1 + ib;
+  const T* v1q = a.v1 + ib;
   const T* v2q = a.v2 + ib;
   const T* v3q = a.v3 + ib;
-  const T* v4q = a.v4 + ib;
   const T* uq = a.u + ib;
-  T* wq = a.w_out + ib;
-  T* v1q = a.v1_out + ib;
-  T tx[4], ty[4], p1[4], v2[4], v3[4], v4[4], uu[4];
+  T* wq = a.w + ib;
+  T* voq = a.v_out + ib;
+  T w[4], tx[4], ty[4], v1[4], v2[4], v3[4], uu[4];
   uint32_t off[4];
   bool gv[4];
   lane_offsets<T>(G, t, off, gv);
   if constexpr (kVecLane<T>) {
+    ld4<NT>(static_cast<const T*>(wq), off, gv, w);
     ld4<NT>(txq, off, gv, tx);
     ld4<NT>(tyq, off, gv, ty);
-    ld4<NT>(static_cast<const T*>(p1q), off, gv, p1);
+    ld4<NT>(v1q, off, gv, v1);
     ld4<NT>(v2q, off, gv, v2);
     ld4<NT>(v3q, off, gv, v3);
-    ld4<NT>(v4q, off, gv, v4);
     ld4<NT>(uq, off, gv, uu);
   } else {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      tx[v] = ty[v] = p1[v] = v2[v] = v3[v] = v4[v] = uu[v] = T(0);
+      w[v] = tx[v] = ty[v] = v1[v] = v2[v] = v3[v] = uu[v] = T(0);
       if (gv[v]) {
-        tx[v] = ldo<NT>(txq, off[v]); ty[v] = ldo<NT>(tyq, off[v]); p1[v] = ldo<NT>(p1q, off[v]);
-        v2[v] = ldo<NT>(v2q, off[v]); v3[v] = ldo<NT>(v3q, off[v]); v4[v] = ldo<NT>(v4q, off[v]);
+        w[v] = ldo<NT>(static_cast<const T*>(wq), off[v]);
+        tx[v] = ldo<NT>(txq, off[v]); ty[v] = ldo<NT>(tyq, off[v]);
+        v1[v] = ldo<NT>(v1q, off[v]); v2[v] = ldo<NT>(v2q, off[v]); v3[v] = ldo<NT>(v3q, off[v]);
         uu[v] = ldo<NT>(uq, off[v]);
       }
     }
@@ -538,16 +543,33 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_adj_kernel(NodeAdj
     gb0 = a.gb[(int64_t)q * Nn + gn];
   }
 
-  // ubar^{n+1}, then v^{n+1} = P^T ubar^{n+1} on boundary nodes
-  const double cdt = a.cdt;
-  T v1[4];
+  // W w^n on the MFMA
 #pragma unroll
-  for (int v = 0; v < 4; ++v) v1[v] = T((double)p1[v] - cdt * ((double)tx[v] + (double)ty[v]));
-  // boundary tables of the lane's 4 slots (transposed rules, detector
-  // injection) requested at once
+  for (int v = 0; v < 4; ++v) Bs[lane_slot<T>(t, v) * 16 + t.node] = w[v];
+  __syncthreads();
+  const typename Mfma<T>::acc_t S = scatter_tile<T, RTC>(Bs, af, a.Wt, G, t);
+
+  // P1^n and ubar^n, the gradient products
+  const double cdt = a.cdt;
+  const T cdtT = T(cdt);
   const bool wave_bnd = __ballot(t.bnd) != 0;
-  T injv[4] = {T(0), T(0), T(0), T(0)};
-  if (wave_bnd) {
+  T vn[4];
+  double pa = 0.0, pb = 0.0;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    pa += (double)uu[v] * (double)w[v];
+    pb += (double)uu[v] * ((double)S[v] - (double)w[v]);
+  }
+  auto ubar = [&](int v, T inj) {
+    const T p1 = v1[v] + cdtT * (B * S[v] - (A + B) * w[v]) + inj;
+    return T((double)p1 - cdt * ((double)tx[v] + (double)ty[v]));
+  };
+  if (!wave_bnd) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) vn[v] = ubar(v, T(0));
+  } else {
+    // boundary tables of the lane's 4 slots (transposed rules, detector
+    // injection) requested at once; v^n = P^T ubar^n on boundary nodes
     const int tyn = t.bnd ? node_type(t.j, t.i, G.nx, G.ny) : 0;
     const int64_t ib4 = ((int64_t)q * G.K1 + a.step) * 4;
     const double g0 = (t.bnd && t.i == 0) ? a.inj[(ib4 + 0) * G.npos + t.j] : 0.0;
@@ -555,6 +577,7 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_adj_kernel(NodeAdj
     const double g2 = (t.bnd && t.j == 0) ? a.inj[(ib4 + 2) * G.npos + t.i] : 0.0;
     const double g3 = (t.bnd && t.j == G.ny - 1) ? a.inj[(ib4 + 3) * G.npos + t.i] : 0.0;
     BcRuleT rt[4];
+    T injv[4] = {T(0), T(0), T(0), T(0)};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int s = lane_slot<T>(t, v);
@@ -571,51 +594,36 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_adj_kernel(NodeAdj
         injv[v] = p;
       }
     }
-    const T vc[4] = {v1[0], v1[1], v1[2], v1[3]};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) vn[v] = ubar(v, injv[v]);
+    const T vc[4] = {vn[0], vn[1], vn[2], vn[3]};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const T t0 = group_peer(vc, v, rt[v].tgt[0] & 3, t);
       const T t1 = group_peer(vc, v, rt[v].tgt[1] & 3, t);
       if (t.bnd && gv[v]) {
-        T val = rt[v].is_target ? T(0) : v1[v];
+        T val = rt[v].is_target ? T(0) : vn[v];
         if (rt[v].ntgt > 0) val += T(rt[v].coef[0]) * t0;
         if (rt[v].ntgt > 1) val += T(rt[v].coef[1]) * t1;
-        v1[v] = val;
+        vn[v] = val;
       }
     }
   }
 
-  // w^n, and W w on the MFMA
-  T w[4];
+  // w^{n-1} and the stores
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    w[v] = T(kChi0) * v1[v] + T(kChi1) * v2[v] + T(kChi2) * v3[v] + T(kChi3) * v4[v];
-    Bs[lane_slot<T>(t, v) * 16 + t.node] = w[v];
-  }
-  __syncthreads();
-  const typename Mfma<T>::acc_t S = scatter_tile<T, RTC>(Bs, af, a.Wt, G, t);
-
-  // P1^n, stores and the gradient products
-  const T cdtT = T(cdt);
-  double pa = 0.0, pb = 0.0;
-  T pn[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    pn[v] = v1[v] + cdtT * (B * S[v] - (A + B) * w[v]) + injv[v];
+    w[v] = T(kChi0) * vn[v] + T(kChi1) * v1[v] + T(kChi2) * v2[v] + T(kChi3) * v3[v];
     if constexpr (!kVecLane<T>) {
       if (gv[v]) {
-        sto<NT>(p1q, off[v], pn[v]);
         sto<NT>(wq, off[v], w[v]);
-        sto<NT>(v1q, off[v], v1[v]);
+        sto<NT>(voq, off[v], vn[v]);
       }
     }
-    pa += (double)uu[v] * (double)w[v];
-    pb += (double)uu[v] * ((double)S[v] - (double)w[v]);
   }
   if constexpr (kVecLane<T>) {
-    st4<NT>(p1q, off, gv, pn);
     st4<NT>(wq, off, gv, w);
-    st4<NT>(v1q, off, gv, v1);
+    st4<NT>(voq, off, gv, vn);
   }
   pa += __shfl_xor(pa, 16);
   pb += __shfl_xor(pb, 16);
@@ -747,10 +755,10 @@ static void launch_node_adj_rt(const NodeAdjArgs<T>& a, dim3 grid, dim3 block, s
 template <typename T>
 static hipError_t node_adj_t(const Plan& p, const NodeAdjLaunch& L, hipStream_t s) {
   NodeAdjArgs<T> a;
-  a.atx = (const T*)L.atx; a.aty = (const T*)L.aty; a.ap1 = (T*)L.ap1; a.v1_out = (T*)L.v1_out;
-  a.v2 = (const T*)L.v2; a.v3 = (const T*)L.v3; a.v4 = (const T*)L.v4; a.u = (const T*)L.u;
+  a.atx = (const T*)L.atx; a.aty = (const T*)L.aty; a.w = (T*)L.w; a.v_out = (T*)L.v_out;
+  a.v1 = (const T*)L.v1; a.v2 = (const T*)L.v2; a.v3 = (const T*)L.v3; a.u = (const T*)L.u;
   a.mu_a = (const T*)L.mu_a; a.mu_s = (const T*)L.mu_s; a.inj = L.inj;
-  a.w_out = (T*)L.w_out; a.ga = L.ga; a.gb = L.gb;
+  a.ga = L.ga; a.gb = L.gb;
   a.Wt = p.dev.Wt; a.bct = p.dev.bct; a.kappa = p.dev.kappa;
   a.geo = make_geom(p);
   a.step = L.step;

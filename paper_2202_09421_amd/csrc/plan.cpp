@@ -617,11 +617,10 @@ int64_t state_stride_bytes(const Plan& p) {
 }
 
 struct Layout {
-  int64_t states, ckpts, work_u, lring, tx, ty, vring, atx, aty, ap1, flux, ga, gb, gbar, scratch, total;
+  int64_t states, ckpts, work_u, lring, tx, ty, vring, atx, aty, w, flux, ga, gb, gbar, scratch, total;
 };
 
-// Forward: lring[3], tx, ty.  Adjoint: vring[4], w (aliases tx), the carries
-// atx, aty, ap1.  With every state kept no forward step runs during the
+// Forward: lring[3], tx, ty.  Adjoint: vring[4], the carries w, atx, aty.  With every state kept no forward step runs during the
 // adjoint, so vring[0..2] alias the L ring and atx aliases ty; with
 // checkpoints the segment replays need the forward arrays while the adjoint
 // ring and carries are live, so those are separate.
@@ -649,7 +648,7 @@ static Layout layout(const Plan& p, bool adj) {
   if (adj && ck) o += S;
   L.aty = o;
   if (adj) o += S;
-  L.ap1 = o;
+  L.w = o;
   if (adj) o += S;
   L.flux = o;
   o += align256(p.Nq * (p.K + 1) * 4 * p.npos * 8);
@@ -693,9 +692,8 @@ bool map_workspace(const Plan& p, void* base, int64_t bytes, bool adj, Workspace
       ws->vring[3] = b + L.vring;
       ws->atx = ws->ty;
     }
-    ws->wbuf = ws->tx;
     ws->aty = b + L.aty;
-    ws->ap1 = b + L.ap1;
+    ws->wbuf = b + L.w;
     ws->ga = reinterpret_cast<double*>(b + L.ga);
     ws->gb = reinterpret_cast<double*>(b + L.gb);
     ws->gbar = reinterpret_cast<double*>(b + L.gbar);

@@ -162,11 +162,10 @@ struct Workspace {
   void* tx = nullptr;        // forward: -xi Dx u^n
   void* ty = nullptr;        // forward: -eta Dy u^n
   void* vring[4] = {nullptr, nullptr, nullptr, nullptr};  // adjoint ring v^k
-  void* wbuf = nullptr;      // adjoint w^n (aliases tx: live only inside one adjoint step)
-  // adjoint carries from step n+1 to step n: ubar^{n+1} = ap1 - c dt (atx + aty)
-  void* atx = nullptr;       // Dx^T(xi w^{n+1})
-  void* aty = nullptr;       // Dy^T(eta w^{n+1})
-  void* ap1 = nullptr;       // v^{n+2} + c dt (b W w - (a+b) w)^{n+1} + D_e^T Gbar
+  // adjoint carries into step n
+  void* wbuf = nullptr;      // w^n
+  void* atx = nullptr;       // Dx^T(xi w^n)
+  void* aty = nullptr;       // Dy^T(eta w^n)
   double* flux = nullptr;    // [Nq][K+1][4][npos] detector flux / adjoint injection
   double* ga = nullptr;      // [Nq][ny*nx]
   double* gb = nullptr;
@@ -236,18 +235,17 @@ struct NodeFwdLaunch {
 hipError_t launch_node_fwd(const Plan& p, const NodeFwdLaunch& L, hipStream_t s);
 
 struct NodeAdjLaunch {
-  const void* atx;     // pieces of ubar^{n+1}: ap1 - c dt (atx + aty)
-  const void* aty;
-  void* ap1;           // read as P1^{n+1}, overwritten with P1^n
-  void* v1_out;        // ring slot for v^{n+1} = P^T ubar^{n+1}
-  const void* v2;      // v^{n+2}
+  const void* atx;     // Dx^T(xi w^n)
+  const void* aty;     // Dy^T(eta w^n)
+  void* w;             // read as w^n, overwritten with w^{n-1}
+  void* v_out;         // ring slot for v^n = P^T ubar^n
+  const void* v1;      // v^{n+1}
+  const void* v2;
   const void* v3;
-  const void* v4;
   const void* u;       // u^n
   const void* mu_a;
   const void* mu_s;
   const double* inj;   // [Nq][K+1][4][npos] detector injection
-  void* w_out;         // w^n
   double* ga;          // [Nq][ny*nx]
   double* gb;
   int step;            // n
