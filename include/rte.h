@@ -194,7 +194,9 @@ int rte_gradient(rte_plan* plan, const void* mu_a, const void* mu_s, const doubl
  * combination chunk the forward start, K forward steps, the misfit, the
  * adjoint start and then K adjoint steps (every state kept) or, per
  * checkpoint segment from the last, the checkpoint restore, the replayed
- * forward steps and the adjoint steps; and a final reduction of the gradient
+ * forward steps and the adjoint steps (the restore enqueues nothing, since a
+ * replay reads its checkpoint in place, nor does the replay of the last
+ * segment, whose states are still stored); and a final reduction of the gradient
  * over the sources.  rte_gradient_range enqueues the operations with index
  * in [first, last), with the arguments of rte_gradient.  The ranges of one
  * gradient must be enqueued in order from first = 0 with identical

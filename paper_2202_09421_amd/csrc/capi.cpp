@@ -66,21 +66,58 @@ int guard_check(Plan& p, hipStream_t st, const std::vector<Out>& outs) {
     RTE_CHECK(prof_end(stop_, c.st));             \
   } while (0)
 
+// Where the arrays of a chunk's forward live.  Checkpoints are written in
+// place: checkpoint j (u^n, L^{n-1}, L^{n-2}, L^{n-3} of n = j s) is where those
+// arrays are computed and where the later steps, and the replay, read them, so
+// nothing is copied.  States of the last segment go straight to the segment
+// store.  The history before step 0 is one zero array (L^{-1}, also read as
+// L^{-2} and L^{-3}) unless the caller gave start-up states.
+struct Store {
+  const Plan& p;
+  const Workspace& ws;
+  int64_t S;
+  bool save;
+  bool start_up = false;   // L^{-1..-3} of given states are in the ring
+
+  bool ck() const { return save && p.ckpt_every > 0; }
+  int nseg() const { return (int)((p.K + p.ckpt_every - 1) / p.ckpt_every); }
+  void* ckpt(int64_t j, int k) const { return at(ws.ckpts, 4 * j + k, S); }
+
+  void* u(int n) const {
+    if (!ck()) return save ? at(ws.states, n, S) : ws.work_u[n & 1];
+    const int s = (int)p.ckpt_every;
+    if (n < p.K && n % s == 0) return ckpt(n / s, 0);
+    const int last = (nseg() - 1) * s;
+    return n > last ? at(ws.states, n - last, S) : ws.work_u[n & 1];
+  }
+  // L^m belongs to the first checkpoint n > m if that is at most 3 steps on
+  // (a later one finds it there)
+  void* L(int m) const {
+    if (m < 0 && start_up) return ws.lring[m + 3];
+    if (m < 0) m = -1;
+    if (ck()) {
+      const int s = (int)p.ckpt_every, n = m < 0 ? 0 : (m / s + 1) * s;
+      if (n < p.K && n - m <= 3) return ckpt(n / s, n - m);
+    }
+    return ws.lring[(m + 3) % 3];
+  }
+};
+
 // One forward step u^n -> u^{n+1}: x and y lines (one launch), node update.
-int fwd_step(Ctx& c, int n, const void* un, void* unp1, double* flux) {
+int fwd_step(Ctx& c, const Store& st, int n, const void* un, void* unp1, double* flux) {
   LineLaunch ll{un, c.ws.tx, c.ws.ty, LINE_FWD, 3};
   TIMED(RTE_K_LINES_FWD, launch_lines(c.p, ll, c.st));
   NodeFwdLaunch nf;
   nf.u = un;
   nf.X = c.ws.tx;
   nf.Y = c.ws.ty;
-  nf.L1 = c.ws.lring[(n + 2) % 3];
-  nf.L2 = c.ws.lring[(n + 1) % 3];
-  nf.L3 = c.ws.lring[n % 3];
+  nf.L1 = st.L(n - 1);
+  nf.L2 = st.L(n - 2);
+  nf.L3 = st.L(n - 3);
   nf.mu_a = c.mu_a;
   nf.mu_s = c.mu_s;
   nf.u_out = unp1;
-  nf.L_out = c.ws.lring[n % 3];
+  nf.L_out = st.L(n);
   nf.flux = flux;
   nf.step = n;
   if (c.ext) {
@@ -95,14 +132,18 @@ int fwd_step(Ctx& c, int n, const void* un, void* unp1, double* flux) {
 // step n and w^{n-1}), then the transposed line derivatives of w^{n-1}, which
 // step n - 1 reads (none follows step 1).
 int adj_step(Ctx& c, int n, const void* un) {
+  // v^{K+1..K+3} and the transposes of w^K are zero: one zero array
+  const int K = (int)c.p.K;
+  void* zero = c.ws.vring[(K + 1) % 4];
+  auto v = [&](int k) { return k > K ? zero : c.ws.vring[k % 4]; };
   NodeAdjLaunch na;
-  na.atx = c.ws.atx;
-  na.aty = c.ws.aty;
+  na.atx = n == K ? zero : c.ws.atx;
+  na.aty = n == K ? zero : c.ws.aty;
   na.w = c.ws.wbuf;
   na.v_out = c.ws.vring[n % 4];
-  na.v1 = c.ws.vring[(n + 1) % 4];
-  na.v2 = c.ws.vring[(n + 2) % 4];
-  na.v3 = c.ws.vring[(n + 3) % 4];
+  na.v1 = v(n + 1);
+  na.v2 = v(n + 2);
+  na.v3 = v(n + 3);
   na.u = un;
   na.mu_a = c.mu_a;
   na.mu_s = c.mu_s;
@@ -133,9 +174,12 @@ void reset_chunk(const Plan& p) {
 }
 
 // The workspace now holds the saved forward of every source; the states of
-// the last chunk are resident.
-void mark_saved(Plan& p, const void* wsp) {
+// the last chunk are resident.  last_segment: with checkpoints, the segment
+// store still holds the last segment (a forward just ended, or there is only
+// one segment, which no adjoint overwrites).
+void mark_saved(Plan& p, const void* wsp, bool last_segment) {
   p.have_forward = true;
+  p.last_segment = last_segment || p.K <= p.ckpt_every;
   p.saved_chunk = n_chunks(p) - 1;
   p.saved_K = p.K;
   p.saved_ws = wsp;
@@ -157,62 +201,36 @@ int map_or_fail(const Plan& p, void* wsp, int64_t wsb, bool adj, Workspace* ws) 
 }
 
 // Forward of the current chunk, in pieces: start (zero history, u^0 = 0) and
-// step n (with its checkpoint copy when due).  State u^n lives in the state
-// store when every state is kept, else in the ping-pong pair.
-void* fwd_state(const Ctx& c, bool store_all, int n) {
-  return store_all ? at(c.ws.states, n, c.S) : c.ws.work_u[n & 1];
-}
-
-int forward_start(Ctx& c, bool save) {
-  const bool store_all = save && c.p.ckpt_every == 0;
-  for (int k = 0; k < 3; ++k) RTE_CHECK(launch_zero(c.ws.lring[k], c.S, c.st));
-  RTE_CHECK(launch_zero(fwd_state(c, store_all, 0), c.S, c.st));
+// step n.
+int forward_start(Ctx& c, const Store& st) {
+  RTE_CHECK(launch_zero(st.L(-1), c.S, c.st));
+  RTE_CHECK(launch_zero(st.u(0), c.S, c.st));
   return RTE_OK;
 }
 
-int forward_op(Ctx& c, bool save, int n) {
-  const bool store_all = save && c.p.ckpt_every == 0;
-  const int64_t s = c.p.ckpt_every, S = c.S;
-  void* un = fwd_state(c, store_all, n);
-  if (save && s > 0 && n % s == 0) {
-    void* ck = at(c.ws.ckpts, (n / s) * 4, S);
-    RTE_CHECK(launch_copy(ck, un, S, c.st));
-    RTE_CHECK(launch_copy(at(ck, 1, S), c.ws.lring[(n + 2) % 3], S, c.st));
-    RTE_CHECK(launch_copy(at(ck, 2, S), c.ws.lring[(n + 1) % 3], S, c.st));
-    RTE_CHECK(launch_copy(at(ck, 3, S), c.ws.lring[n % 3], S, c.st));
-  }
-  return fwd_step(c, n, un, fwd_state(c, store_all, n + 1), c.ws.flux);
-}
+int forward_op(Ctx& c, const Store& st, int n) { return fwd_step(c, st, n, st.u(n), st.u(n + 1), c.ws.flux); }
 
 // Time loop of the forward for the current chunk (u^0 = 0, zero history);
 // writes the chunk's detector flux; keeps states or checkpoints when save.
 int forward_chunk(Ctx& c, bool save, void* u_final) {
-  if (int rc = forward_start(c, save)) return rc;
+  const Store st{c.p, c.ws, c.S, save};
+  if (int rc = forward_start(c, st)) return rc;
   for (int n = 0; n < c.p.K; ++n)
-    if (int rc = forward_op(c, save, n)) return rc;
-  if (u_final) RTE_CHECK(launch_unpermute(c.p, fwd_state(c, save && c.p.ckpt_every == 0, (int)c.p.K), u_final, c.st));
+    if (int rc = forward_op(c, st, n)) return rc;
+  if (u_final) RTE_CHECK(launch_unpermute(c.p, st.u((int)c.p.K), u_final, c.st));
   return RTE_OK;
 }
 
-// Adjoint of the current chunk in pieces: start (zero ring and carries:
-// w^K = 0, v^{K+1..K+3} = 0), the restore of checkpoint j at the start
-// of segment j (checkpoint mode), and step n given u^n.
+// Replay step k of the segment that starts at k0
+int replay_op(Ctx& c, const Store& st, int k0, int k) {
+  return fwd_step(c, st, k, k == k0 ? st.u(k0) : at(c.ws.states, k - k0, c.S), at(c.ws.states, k + 1 - k0, c.S), nullptr);
+}
+
+// Adjoint of the current chunk in pieces: start (w^K = 0 and the zero array of
+// adj_step) and step n given u^n.
 int adjoint_start(Ctx& c) {
-  for (int k = 0; k < 4; ++k) RTE_CHECK(launch_zero(c.ws.vring[k], c.S, c.st));
-  RTE_CHECK(launch_zero(c.ws.atx, c.S, c.st));
-  RTE_CHECK(launch_zero(c.ws.aty, c.S, c.st));
+  RTE_CHECK(launch_zero(c.ws.vring[(c.p.K + 1) % 4], c.S, c.st));
   RTE_CHECK(launch_zero(c.ws.wbuf, c.S, c.st));
-  return RTE_OK;
-}
-
-int segment_restore(Ctx& c, int j) {
-  const int64_t S = c.S;
-  const int k0 = j * (int)c.p.ckpt_every;
-  void* ck = at(c.ws.ckpts, (int64_t)j * 4, S);
-  RTE_CHECK(launch_copy(c.ws.states, ck, S, c.st));
-  RTE_CHECK(launch_copy(c.ws.lring[(k0 + 2) % 3], at(ck, 1, S), S, c.st));
-  RTE_CHECK(launch_copy(c.ws.lring[(k0 + 1) % 3], at(ck, 2, S), S, c.st));
-  RTE_CHECK(launch_copy(c.ws.lring[k0 % 3], at(ck, 3, S), S, c.st));
   return RTE_OK;
 }
 
@@ -231,8 +249,10 @@ struct OpCursor {
 // states (or checkpoints) are in the workspace and whose detector injection
 // is in ws.flux; accumulates the chunk's gradient partials into ga, gb.
 // Operations: start, then K adjoint steps (every state kept) or, per
-// segment from the last, the restore, the replay steps and the adjoint steps.
-int adjoint_ops(Ctx& c, OpCursor& r) {
+// segment from the last, the restore (nothing to do: the replay reads the
+// checkpoint where it lies), the replay steps and the adjoint steps.  The last
+// segment is not replayed while the segment store still holds it.
+int adjoint_ops(Ctx& c, OpCursor& r, bool last_segment) {
   Plan& p = c.p;
   const int64_t S = c.S;
   const int K = (int)p.K;
@@ -244,15 +264,16 @@ int adjoint_ops(Ctx& c, OpCursor& r) {
         if (int rc = adj_step(c, n, at(c.ws.states, n, S))) return rc;
     return RTE_OK;
   }
+  const Store st{p, c.ws, S, true};
   const int s = (int)p.ckpt_every;
-  const int nseg = (K + s - 1) / s;
+  const int nseg = st.nseg();
   for (int j = nseg - 1; j >= 0; --j) {
     const int k0 = j * s, k1 = std::min(k0 + s, K);
-    if (r.take())
-      if (int rc = segment_restore(c, j)) return rc;
+    const bool replay = j < nseg - 1 || !last_segment;
+    (void)r.take();
     for (int k = k0; k < k1; ++k)
-      if (r.take())
-        if (int rc = fwd_step(c, k, at(c.ws.states, k - k0, S), at(c.ws.states, k + 1 - k0, S), nullptr)) return rc;
+      if (r.take() && replay)
+        if (int rc = replay_op(c, st, k0, k)) return rc;
     for (int n = k1; n > k0; --n)
       if (r.take())
         if (int rc = adj_step(c, n, at(c.ws.states, n - k0, S))) return rc;
@@ -260,9 +281,9 @@ int adjoint_ops(Ctx& c, OpCursor& r) {
   return RTE_OK;
 }
 
-int adjoint_chunk(Ctx& c) {
+int adjoint_chunk(Ctx& c, bool last_segment) {
   OpCursor r{0, INT64_MAX, 0};
-  return adjoint_ops(c, r);
+  return adjoint_ops(c, r, last_segment);
 }
 
 int run_forward(Plan& p, const void* mu_a, const void* mu_s, double* G, void* u_final, int save, void* wsp,
@@ -285,7 +306,7 @@ int run_forward(Plan& p, const void* mu_a, const void* mu_s, double* G, void* u_
     }
   }
   reset_chunk(p);
-  if (save) mark_saved(p, wsp);
+  if (save) mark_saved(p, wsp, true);
   return RTE_OK;
 }
 
@@ -309,12 +330,14 @@ int run_adjoint(Plan& p, const void* mu_a, const void* mu_s, const double* Gbar,
   RTE_CHECK(launch_zero(ws.ga, gbytes, st));
   RTE_CHECK(launch_zero(ws.gb, gbytes, st));
   const int64_t nc = n_chunks(p);
+  const bool resident = p.last_segment;
+  p.last_segment = false;
   for (int64_t i = 0; i < nc; ++i) {
     const int64_t k = (p.saved_chunk + nc - i) % nc;  // saved chunk first
     set_chunk(p, k);
     int rc = (i == 0) ? RTE_OK : forward_chunk(c, true, nullptr);
     if (rc == RTE_OK && launch_inject(p, Gbar, ws.flux, (int)p.K, st) != hipSuccess) rc = RTE_EDEVICE;
-    if (rc == RTE_OK) rc = adjoint_chunk(c);
+    if (rc == RTE_OK) rc = adjoint_chunk(c, i > 0 || resident);
     if (rc != RTE_OK) {
       reset_chunk(p);
       if (rc == RTE_EDEVICE && last_error()[0] == '\0') set_error("injection kernel launch failed");
@@ -322,6 +345,7 @@ int run_adjoint(Plan& p, const void* mu_a, const void* mu_s, const double* Gbar,
     }
   }
   p.saved_chunk = (p.saved_chunk + 1) % nc;  // the last chunk processed
+  p.last_segment = p.K <= p.ckpt_every;
   reset_chunk(p);
   RTE_CHECK(launch_grad_reduce(p, ws.ga, ws.gb, da, db, st));
   return RTE_OK;
@@ -355,13 +379,14 @@ int psi_step(Ctx& c, const PsiArrays& A, int k, const void* upair) {
   nf.u = in;
   nf.X = A.X;
   nf.Y = A.Y;
-  nf.L1 = A.lr[(k + 2) % 3];
-  nf.L2 = A.lr[(k + 1) % 3];
-  nf.L3 = A.lr[k % 3];
+  auto L = [&](int m) { return A.lr[m < 0 ? 2 : m % 3]; };   // zero history: one array
+  nf.L1 = L(k - 1);
+  nf.L2 = L(k - 2);
+  nf.L3 = L(k - 3);
   nf.mu_a = c.mu_a;
   nf.mu_s = c.mu_s;
   nf.u_out = A.psi[(k + 1) & 1];
-  nf.L_out = A.lr[k % 3];
+  nf.L_out = L(k);
   nf.flux = nullptr;
   nf.step = k;
   nf.csrc = c.ws.flux;
@@ -382,7 +407,7 @@ int cadj_chunk(Ctx& c) {
   const int K = (int)p.K;
   const PsiArrays A = psi_arrays(p, ws);
   RTE_CHECK(launch_zero(A.psi[0], S, st));
-  for (int k = 0; k < 3; ++k) RTE_CHECK(launch_zero(A.lr[k], S, st));
+  RTE_CHECK(launch_zero(A.lr[2], S, st));
   if (p.ckpt_every == 0) {
     for (int k = 0; k < K; ++k) {
       int rc = psi_step(c, A, k, at(ws.states, K - k, S));
@@ -390,19 +415,14 @@ int cadj_chunk(Ctx& c) {
     }
     return RTE_OK;
   }
+  const Store fs{p, ws, S, true};
   const int s = (int)p.ckpt_every;
-  const int nseg = (K + s - 1) / s;
+  const int nseg = fs.nseg();
   for (int j = nseg - 1; j >= 0; --j) {
     const int k0 = j * s, k1 = std::min(k0 + s, K);
-    void* ck = at(ws.ckpts, (int64_t)j * 4, S);
-    RTE_CHECK(launch_copy(ws.states, ck, S, st));
-    RTE_CHECK(launch_copy(ws.lring[(k0 + 2) % 3], at(ck, 1, S), S, st));
-    RTE_CHECK(launch_copy(ws.lring[(k0 + 1) % 3], at(ck, 2, S), S, st));
-    RTE_CHECK(launch_copy(ws.lring[k0 % 3], at(ck, 3, S), S, st));
-    for (int k = k0; k < k1; ++k) {
-      int rc = fwd_step(c, k, at(ws.states, k - k0, S), at(ws.states, k + 1 - k0, S), nullptr);
-      if (rc != RTE_OK) return rc;
-    }
+    if (j < nseg - 1)   // the last segment is still in the store
+      for (int k = k0; k < k1; ++k)
+        if (int rc = replay_op(c, fs, k0, k)) return rc;
     for (int n = k1; n > k0; --n) {
       int rc = psi_step(c, A, K - n, at(ws.states, n - k0, S));
       if (rc != RTE_OK) return rc;
@@ -423,15 +443,18 @@ int forward_ex_chunk(Ctx& c, void* u_final) {
   const rte_forward_extra* ex = c.ext;
   const int64_t es = (p.dtype == RTE_F64) ? 8 : 4;
   const int64_t nat = p.nx * p.ny * p.M * es;  // one source, natural layout
-  for (int k = 0; k < 3; ++k) RTE_CHECK(launch_zero(ws.lring[k], S, st));
+  const Store fs{p, ws, S, false, ex->u_hist != nullptr};
   RTE_CHECK(launch_zero(ws.work_u[0], S, st));
+  if (!ex->u_hist) RTE_CHECK(launch_zero(fs.L(-1), S, st));
   if (ex->u_hist) {
+    // each pass reads its own slot as history and discards the update
+    for (int k = 0; k < 3; ++k) RTE_CHECK(launch_zero(ws.lring[k], S, st));
     for (int k = 3; k >= 1; --k) {
       const char* h = static_cast<const char*>(ex->u_hist) + ((int64_t)(k - 1) * p.Nq + p.cq0) * nat;
       RTE_CHECK(launch_permute(p, h, ws.work_u[0], st));
       LineLaunch ll{ws.work_u[0], ws.tx, ws.ty, LINE_FWD, 3};
       TIMED(RTE_K_LINES_FWD, launch_lines(p, ll, st));
-      void* Lk = ws.lring[(3 - k) % 3];  // L^{-k}: ring slot (-k) mod 3
+      void* Lk = fs.L(-k);
       NodeFwdLaunch nf;
       nf.u = ws.work_u[0];
       nf.X = ws.tx;
@@ -464,7 +487,7 @@ int forward_ex_chunk(Ctx& c, void* u_final) {
   };
   if (int rc = snap(0, ws.work_u[0])) return rc;
   for (int n = 0; n < p.K; ++n) {
-    int rc = fwd_step(c, n, ws.work_u[n & 1], ws.work_u[(n + 1) & 1], ws.flux);
+    int rc = fwd_step(c, fs, n, ws.work_u[n & 1], ws.work_u[(n + 1) & 1], ws.flux);
     if (rc == RTE_OK) rc = snap(n + 1, ws.work_u[(n + 1) & 1]);
     if (rc != RTE_OK) return rc;
   }
@@ -529,6 +552,7 @@ int enqueue_gradient_ops(Plan& p, const GradArgs& a, hipStream_t st, int64_t fir
   OpCursor r{first, last, 0};
   const int64_t nc = n_chunks(p);
   const int K = (int)p.K;
+  const Store fs{p, ws, S, true};
   auto body = [&]() -> int {
     if (r.take()) {
       p.have_forward = false;
@@ -540,10 +564,10 @@ int enqueue_gradient_ops(Plan& p, const GradArgs& a, hipStream_t st, int64_t fir
     for (int64_t k = 0; k < nc; ++k) {
       set_chunk(p, k);
       if (r.take())
-        if (int rc = forward_start(c, true)) return rc;
+        if (int rc = forward_start(c, fs)) return rc;
       for (int n = 0; n < K; ++n)
         if (r.take())
-          if (int rc = forward_op(c, true, n)) return rc;
+          if (int rc = forward_op(c, fs, n)) return rc;
       if (r.take()) {
         hipError_t e = launch_detect(p, ws.flux, a.G, K, st);
         if (e == hipSuccess) e = launch_misfit(p, a.G, a.G_meas, ws.gbar, a.J, K, st);
@@ -553,12 +577,12 @@ int enqueue_gradient_ops(Plan& p, const GradArgs& a, hipStream_t st, int64_t fir
           return RTE_EDEVICE;
         }
       }
-      if (int rc = adjoint_ops(c, r)) return rc;
+      if (int rc = adjoint_ops(c, r, true)) return rc;
     }
     reset_chunk(p);
     if (r.take()) {
       RTE_CHECK(launch_grad_reduce(p, ws.ga, ws.gb, a.dmu_a, a.dmu_s, st));
-      mark_saved(p, a.ws);
+      mark_saved(p, a.ws, false);
     }
     return RTE_OK;
   };
@@ -613,7 +637,7 @@ int enqueue_gradient_continuous(Plan& p, const GradArgs& a, hipStream_t st) {
   }
   reset_chunk(p);
   RTE_CHECK(launch_grad_reduce(p, ws.ga, ws.gb, a.dmu_a, a.dmu_s, st));
-  mark_saved(p, a.ws);
+  mark_saved(p, a.ws, false);
   return RTE_OK;
 }
 
@@ -647,7 +671,7 @@ int graph_gradient(Plan& p, const GradArgs& a, hipStream_t st) {
     p.gkey_sched = p.sched_version;
   }
   RTE_CHECK(hipGraphLaunch(p.gexec, st));
-  mark_saved(p, a.ws);
+  mark_saved(p, a.ws, false);
   return RTE_OK;
 }
 
@@ -1219,7 +1243,7 @@ int rte_batch_gradient(rte_batch* h, const void* const* mu_a, const void* const*
       b.key = key;
     }
     RTE_CHECK(hipGraphLaunch(b.gexec, st));
-    for (size_t i = 0; i < n; ++i) mark_saved(*b.plans[i], args[i].ws);
+    for (size_t i = 0; i < n; ++i) mark_saved(*b.plans[i], args[i].ws, false);
     for (size_t i = 0; i < n; ++i)
       if (int rc = guard_check(*b.plans[i], st, grad_outputs(*b.plans[i], args[i]))) return rc;
     return RTE_OK;

@@ -931,29 +931,16 @@ hipError_t launch_nonfinite(const double* x, int64_t n, unsigned long long* flag
   return hipGetLastError();
 }
 
-// Zero fill and device copy as kernels (8-byte words): graph captures of the
-// step sequence then hold only kernel nodes.
+// Zero fill as a kernel (8-byte words): graph captures of the step sequence
+// then hold only kernel nodes.
 __global__ void fill_zero_kernel(unsigned long long* __restrict__ p, int64_t n) {
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) p[t] = 0ull;
 }
-__global__ void copy_words_kernel(unsigned long long* __restrict__ d, const unsigned long long* __restrict__ s, int64_t n) {
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) d[t] = s[t];
-}
-
 hipError_t launch_zero(void* p, int64_t bytes, hipStream_t s) {
   const int64_t n = bytes / 8;
   if (n <= 0) return hipSuccess;
   const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
   hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, s, (unsigned long long*)p, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy(void* d, const void* src, int64_t bytes, hipStream_t s) {
-  const int64_t n = bytes / 8;
-  if (n <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
-  hipLaunchKernelGGL(copy_words_kernel, dim3(blocks), dim3(256), 0, s, (unsigned long long*)d,
-                     (const unsigned long long*)src, n);
   return hipGetLastError();
 }
 

@@ -126,6 +126,7 @@ struct Plan {
   bool line_nt = false;        // the same for the line passes' stores (kLineNtBytes)
   int64_t saved_chunk = -1;    // chunk whose forward states are in the workspace
   bool have_forward = false;   // a saved forward lives in the workspace
+  bool last_segment = false;   // its last checkpoint segment's states are still in the segment store
   int64_t saved_K = 0;
   const void* saved_ws = nullptr;  // workspace base of the saved forward
   // staged gradient (rte_gradient_range): next op expected and the
@@ -155,7 +156,7 @@ struct Workspace {
   char* base = nullptr;
   int64_t bytes = 0;
   // state-sized arrays (plan dtype), each Nq*M*ny*nx elements
-  void* states = nullptr;    // store-all: (K+1) states; checkpoint: segment store (s+1)
+  void* states = nullptr;    // store-all: (K+1) states; checkpoint: segment store (s+1; entry 0 unused)
   void* ckpts = nullptr;     // checkpoint mode: n_ckpt * 4 states (u, L1, L2, L3)
   void* work_u[2] = {nullptr, nullptr};  // checkpoint mode: ping-pong current state
   void* lring[3] = {nullptr, nullptr, nullptr};
@@ -273,6 +274,5 @@ hipError_t launch_flux_map(const Plan& p, const void* state, double* out, int64_
 // flag[0] = 1 if any of x[0 .. n) is NaN or infinite (flag left alone otherwise)
 hipError_t launch_nonfinite(const double* x, int64_t n, unsigned long long* flag, hipStream_t s);
 hipError_t launch_zero(void* p, int64_t bytes, hipStream_t s);
-hipError_t launch_copy(void* d, const void* src, int64_t bytes, hipStream_t s);
 
 }  // namespace rte
