@@ -242,7 +242,7 @@ struct NodeFwdArgs {
   const T* u; const T* X; const T* Y; const T* L1; const T* L2; const T* L3;
   const T* mu_a; const T* mu_s;
   T* u_out; T* L_out; double* flux;
-  const double* Wt; const BcRule* bc; const double* kappa;
+  const double* Wt; const int32_t* bc; const double2* bc_coef; const double* kappa;
   const double* beam_sp; const double* beam_an; const double* beam_tt; const int32_t* beam_off;
   // continuous adjoint (CADJ): inflow source table, paired forward state,
   // reversed-ordinate slots, gradient maps, quadrature dtheta dx dy dt
@@ -332,6 +332,7 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_fwd_kernel(NodeFwd
   const T A = t.valid ? a.mu_a[gn] : T(0), B = t.valid ? a.mu_s[gn] : T(0);
   T af[RTC > 0 ? 4 * RTC : 1];
   load_afrag<T, RTC>(af, a.Wt, G, t);
+  const int b0 = a.beam_off[q], b1 = a.beam_off[q + 1];   // the source's beams
 
 #pragma unroll
   for (int v = 0; v < 4; ++v) Bs[lane_slot<T>(t, v) * 16 + t.node] = u[v];
@@ -361,9 +362,12 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_fwd_kernel(NodeFwd
   }
   if constexpr (kVecLane<T>) st4<NT>(Loq, off, gv, Ln);
 
-  // inflow condition with Fresnel reflection and the beams at t_{n+1}.  The
-  // boundary tables (reflection rules, beam factors, detector weights) of the
-  // lane's 4 slots are all requested at once: one memory round trip.
+  // inflow condition with Fresnel reflection and the beams at t_{n+1}.  A wave
+  // with boundary nodes ends last, so its tables (reflection rules, detector
+  // weights, beam factors of the lane's 4 slots) are read without a branch at
+  // clamped indices and masked afterwards: one memory round trip, and one more
+  // per further beam.  With each value behind its own test the trips added up
+  // to a third of a small grid's pass.
   const bool wave_bnd = __ballot(t.bnd) != 0;
   const int wl0 = !t.bnd ? -1 : ((t.i == 0) ? 0 : ((t.i == G.nx - 1) ? 1 : -1));
   const int wl1 = !t.bnd ? -1 : ((t.j == 0) ? 2 : ((t.j == G.ny - 1) ? 3 : -1));
@@ -371,38 +375,56 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_fwd_kernel(NodeFwd
   if (wave_bnd) {
     const int ty = t.bnd ? node_type(t.j, t.i, G.nx, G.ny) : 0;
     const int bp = t.bnd ? boundary_pos(t.j, t.i, G.nx, G.ny) : 0;
-    BcRule br[4];
-    T src[4];
+    int code[4];
+    double2 cf[4];
+    T src[4] = {T(0), T(0), T(0), T(0)};
     double k0[4], k1[4];
-    const int b0 = a.beam_off[q], b1 = a.beam_off[q + 1];
+    int sc[4];
+    bool on[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int s = lane_slot<T>(t, v);
-      const bool on = t.bnd && gv[v];
-      br[v].flag = 0; br[v].src_a = s; br[v].src_b = s; br[v].pad = 0; br[v].coef_a = 0.0; br[v].coef_b = 0.0;
-      if (on) br[v] = a.bc[ty * G.M + s];
-      src[v] = T(0);
-      if constexpr (CADJ) {
-        if (on)
-          src[v] = T((1.0 - br[v].coef_a - br[v].coef_b) *
-                     a.csrc[((int64_t)q * G.K1 + a.step + 1) * 4 * G.npos + bp]);
-      } else if (EXT && a.inflow.rank > 0) {
-        if (on && br[v].flag)
-          src[v] = T(sep_value(a.inflow, a.step + 4, G.K1 + 3, t.i, t.j, G.nx, G.ny, G.M, a.slot_m[s]));
-      } else {
-        if (on && a.step >= 0)
-          for (int b = b0; b < b1; ++b)
-            src[v] += T(a.beam_sp[(int64_t)b * G.nb + bp] * a.beam_an[b * G.M + s]) * T(a.beam_tt[(int64_t)b * G.K1 + a.step + 1]);
+      sc[v] = min(lane_slot<T>(t, v), G.M - 1);
+      on[v] = t.bnd && gv[v];
+      code[v] = a.bc[ty * G.M + sc[v]];
+      cf[v] = a.bc_coef[ty * G.M + sc[v]];
+      k0[v] = k1[v] = 0.0;
+    }
+    if (a.flux) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        k0[v] = a.kappa[max(wl0, 0) * G.M + sc[v]];
+        k1[v] = a.kappa[max(wl1, 0) * G.M + sc[v]];
       }
-      k0[v] = (on && a.flux && wl0 >= 0) ? a.kappa[wl0 * G.M + s] : 0.0;
-      k1[v] = (on && a.flux && wl1 >= 0) ? a.kappa[wl1 * G.M + s] : 0.0;
+    }
+    if constexpr (CADJ) {
+      const double cs = a.csrc[((int64_t)q * G.K1 + a.step + 1) * 4 * G.npos + bp];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) src[v] = T((1.0 - cf[v].x - cf[v].y) * cs);
+    } else if (EXT && a.inflow.rank > 0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (on[v] && (code[v] & 1))
+          src[v] = T(sep_value(a.inflow, a.step + 4, G.K1 + 3, t.i, t.j, G.nx, G.ny, G.M, a.slot_m[sc[v]]));
+    } else if (a.step >= 0) {
+      for (int b = b0; b < b1; ++b) {
+        const double sp = a.beam_sp[(int64_t)b * G.nb + bp];
+        const T tt = T(a.beam_tt[(int64_t)b * G.K1 + a.step + 1]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) src[v] += T(sp * a.beam_an[b * G.M + sc[v]]) * tt;
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (!on[v]) code[v] = 0;
+      if (!on[v] || wl0 < 0) k0[v] = 0.0;
+      if (!on[v] || wl1 < 0) k1[v] = 0.0;
     }
     const T uc[4] = {un[0], un[1], un[2], un[3]};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const T ta = group_peer(uc, v, br[v].src_a & 3, t);
-      const T tb = group_peer(uc, v, br[v].src_b & 3, t);
-      if (br[v].flag) un[v] = T(br[v].coef_a) * ta + T(br[v].coef_b) * tb + src[v];
+      const T ta = group_peer(uc, v, (code[v] >> 1) & 3, t);
+      const T tb = group_peer(uc, v, (code[v] >> 3) & 3, t);
+      if (code[v] & 1) un[v] = T(cf[v].x) * ta + T(cf[v].y) * tb + src[v];
     }
     // detector flux on boundary nodes (FP64): lane partial over its 4
     // groups, then over the 4 slot lanes of the node, then over the row tiles
@@ -478,7 +500,7 @@ struct NodeAdjArgs {
   const T* v1; const T* v2; const T* v3; const T* u;
   const T* mu_a; const T* mu_s; const double* inj;
   double* ga; double* gb;
-  const double* Wt; const BcRuleT* bct; const double* kappa;
+  const double* Wt; const int32_t* bct; const double2* bct_coef; const double* kappa;
   NodeGeom geo;
   int step;
   double cdt;
@@ -568,43 +590,47 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_adj_kernel(NodeAdj
 #pragma unroll
     for (int v = 0; v < 4; ++v) vn[v] = ubar(v, T(0));
   } else {
-    // boundary tables of the lane's 4 slots (transposed rules, detector
-    // injection) requested at once; v^n = P^T ubar^n on boundary nodes
+    // v^n = P^T ubar^n on boundary nodes; the tables (transposed rules, detector
+    // weights of the node's one or two walls, injection) in one round trip, as
+    // in the forward pass
     const int tyn = t.bnd ? node_type(t.j, t.i, G.nx, G.ny) : 0;
+    const int wl0 = !t.bnd ? -1 : ((t.i == 0) ? 0 : ((t.i == G.nx - 1) ? 1 : -1));
+    const int wl1 = !t.bnd ? -1 : ((t.j == 0) ? 2 : ((t.j == G.ny - 1) ? 3 : -1));
     const int64_t ib4 = ((int64_t)q * G.K1 + a.step) * 4;
-    const double g0 = (t.bnd && t.i == 0) ? a.inj[(ib4 + 0) * G.npos + t.j] : 0.0;
-    const double g1 = (t.bnd && t.i == G.nx - 1) ? a.inj[(ib4 + 1) * G.npos + t.j] : 0.0;
-    const double g2 = (t.bnd && t.j == 0) ? a.inj[(ib4 + 2) * G.npos + t.i] : 0.0;
-    const double g3 = (t.bnd && t.j == G.ny - 1) ? a.inj[(ib4 + 3) * G.npos + t.i] : 0.0;
-    BcRuleT rt[4];
-    T injv[4] = {T(0), T(0), T(0), T(0)};
+    const double g0 = a.inj[(ib4 + max(wl0, 0)) * G.npos + (wl0 < 0 ? 0 : t.j)];
+    const double g1 = a.inj[(ib4 + max(wl1, 0)) * G.npos + (wl1 < 0 ? 0 : t.i)];
+    int code[4];
+    double2 cf[4];
+    double k0[4], k1[4];
+    T injv[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int s = lane_slot<T>(t, v);
-      const bool on = t.bnd && gv[v];
-      rt[v].is_target = 0; rt[v].ntgt = 0; rt[v].tgt[0] = s; rt[v].tgt[1] = s; rt[v].coef[0] = 0.0; rt[v].coef[1] = 0.0;
-      if (on) rt[v] = a.bct[tyn * G.M + s];
-      // detector misfit enters through the outgoing boundary entries
-      if (on) {
-        T p = T(0);
-        if (t.i == 0) p += T(a.kappa[0 * G.M + s] * g0);
-        if (t.i == G.nx - 1) p += T(a.kappa[1 * G.M + s] * g1);
-        if (t.j == 0) p += T(a.kappa[2 * G.M + s] * g2);
-        if (t.j == G.ny - 1) p += T(a.kappa[3 * G.M + s] * g3);
-        injv[v] = p;
-      }
+      const int s = min(lane_slot<T>(t, v), G.M - 1);
+      code[v] = a.bct[tyn * G.M + s];
+      cf[v] = a.bct_coef[tyn * G.M + s];
+      k0[v] = a.kappa[max(wl0, 0) * G.M + s];
+      k1[v] = a.kappa[max(wl1, 0) * G.M + s];
+    }
+    // detector misfit enters through the outgoing boundary entries
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      T p = T(0);
+      if (wl0 >= 0) p += T(k0[v] * g0);
+      if (wl1 >= 0) p += T(k1[v] * g1);
+      injv[v] = (t.bnd && gv[v]) ? p : T(0);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) vn[v] = ubar(v, injv[v]);
     const T vc[4] = {vn[0], vn[1], vn[2], vn[3]};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const T t0 = group_peer(vc, v, rt[v].tgt[0] & 3, t);
-      const T t1 = group_peer(vc, v, rt[v].tgt[1] & 3, t);
+      const int ntgt = (code[v] >> 1) & 3;
+      const T t0 = group_peer(vc, v, (code[v] >> 3) & 3, t);
+      const T t1 = group_peer(vc, v, (code[v] >> 5) & 3, t);
       if (t.bnd && gv[v]) {
-        T val = rt[v].is_target ? T(0) : vn[v];
-        if (rt[v].ntgt > 0) val += T(rt[v].coef[0]) * t0;
-        if (rt[v].ntgt > 1) val += T(rt[v].coef[1]) * t1;
+        T val = (code[v] & 1) ? T(0) : vn[v];
+        if (ntgt > 0) val += T(cf[v].x) * t0;
+        if (ntgt > 1) val += T(cf[v].y) * t1;
         vn[v] = val;
       }
     }
@@ -718,7 +744,7 @@ static hipError_t node_fwd_t(const Plan& p, const NodeFwdLaunch& L, hipStream_t 
   a.L1 = (const T*)L.L1; a.L2 = (const T*)L.L2; a.L3 = (const T*)L.L3;
   a.mu_a = (const T*)L.mu_a; a.mu_s = (const T*)L.mu_s;
   a.u_out = (T*)L.u_out; a.L_out = (T*)L.L_out; a.flux = L.flux;
-  a.Wt = p.dev.Wt; a.bc = p.dev.bc; a.kappa = p.dev.kappa;
+  a.Wt = p.dev.Wt; a.bc = p.dev.bc; a.bc_coef = p.dev.bc_coef; a.kappa = p.dev.kappa;
   a.beam_sp = p.dev.beam_sp; a.beam_an = p.dev.beam_an; a.beam_tt = p.dev.beam_tt; a.beam_off = p.dev.beam_off;
   a.csrc = L.csrc; a.upair = (const T*)L.upair; a.slot_rev = p.dev.slot_rev; a.ga = L.ga; a.gb = L.gb;
   a.vsrc = L.vsrc ? *L.vsrc : rte_separable{0, 0, nullptr, nullptr, nullptr};
@@ -759,7 +785,7 @@ static hipError_t node_adj_t(const Plan& p, const NodeAdjLaunch& L, hipStream_t 
   a.v1 = (const T*)L.v1; a.v2 = (const T*)L.v2; a.v3 = (const T*)L.v3; a.u = (const T*)L.u;
   a.mu_a = (const T*)L.mu_a; a.mu_s = (const T*)L.mu_s; a.inj = L.inj;
   a.ga = L.ga; a.gb = L.gb;
-  a.Wt = p.dev.Wt; a.bct = p.dev.bct; a.kappa = p.dev.kappa;
+  a.Wt = p.dev.Wt; a.bct = p.dev.bct; a.bct_coef = p.dev.bct_coef; a.kappa = p.dev.kappa;
   a.geo = make_geom(p);
   a.step = L.step;
   a.cdt = p.prob.c * p.prob.dt;

@@ -274,7 +274,7 @@ static bool validate(const rte_problem* p, const rte_beam* beams, int64_t nbm, c
 }
 
 static void free_tables(DeviceTables& t) {
-  void* ps[] = {t.xi, t.eta, t.Wt, t.bc, t.bct, t.kappa, t.det_w, t.beam_sp, t.beam_an, t.beam_tt, t.beam_off,
+  void* ps[] = {t.xi, t.eta, t.Wt, t.bc, t.bc_coef, t.bct, t.bct_coef, t.kappa, t.det_w, t.beam_sp, t.beam_an, t.beam_tt, t.beam_off,
                 t.slot_m, t.fc_buf, t.det_sp, t.slot_rev, t.guard_flag};
   for (void* p : ps)
     if (p) (void)hipFree(p);
@@ -537,8 +537,17 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   p.sched.node_tiles_per_block = node_tiles_default(p);
   // ---- upload
   std::vector<int32_t> slotm(p.slot_m.begin(), p.slot_m.end());
-  bool ok = upload(xi, &p.dev.xi) && upload(eta, &p.dev.eta) && upload(Wt, &p.dev.Wt) && upload(bc, &p.dev.bc) &&
-            upload(bct, &p.dev.bct) && upload(kappa, &p.dev.kappa) && upload(detw, &p.dev.det_w) &&
+  // packed rules (every slot a rule refers to is in the slot's own group)
+  std::vector<int32_t> bcc(bc.size()), btc(bct.size());
+  std::vector<double2> bcf(bc.size()), btf(bct.size());
+  for (size_t k = 0; k < bc.size(); ++k) {
+    bcc[k] = bc[k].flag | (bc[k].src_a & 3) << 1 | (bc[k].src_b & 3) << 3;
+    bcf[k] = make_double2(bc[k].coef_a, bc[k].coef_b);
+    btc[k] = bct[k].is_target | bct[k].ntgt << 1 | (bct[k].tgt[0] & 3) << 3 | (bct[k].tgt[1] & 3) << 5;
+    btf[k] = make_double2(bct[k].coef[0], bct[k].coef[1]);
+  }
+  bool ok = upload(xi, &p.dev.xi) && upload(eta, &p.dev.eta) && upload(Wt, &p.dev.Wt) && upload(bcc, &p.dev.bc) &&
+            upload(bcf, &p.dev.bc_coef) && upload(btc, &p.dev.bct) && upload(btf, &p.dev.bct_coef) && upload(kappa, &p.dev.kappa) && upload(detw, &p.dev.det_w) &&
             upload(bsp, &p.dev.beam_sp) && upload(ban, &p.dev.beam_an) && upload(btt, &p.dev.beam_tt) &&
             upload(boff, &p.dev.beam_off) && upload(slotm, &p.dev.slot_m) && upload(fcbuf, &p.dev.fc_buf) &&
             upload(detsp, &p.dev.det_sp) && upload(srev, &p.dev.slot_rev) &&

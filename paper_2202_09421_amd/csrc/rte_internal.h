@@ -80,8 +80,13 @@ struct DeviceTables {
   double* xi = nullptr;     // [M]
   double* eta = nullptr;    // [M]
   double* Wt = nullptr;     // [Mpad16][Mpad16] HG matrix in slot order (zero padded)
-  BcRule* bc = nullptr;     // [9][M]
-  BcRuleT* bct = nullptr;   // [9][M]
+  // boundary rules [9][M]: packed flags and slots within the group, and the two
+  // coefficients.  Forward: bit 0 flag, bits 1-2 src_a, 3-4 src_b.  Transpose:
+  // bit 0 is_target, bits 1-2 ntgt, 3-4 tgt[0], 5-6 tgt[1]
+  int32_t* bc = nullptr;
+  double2* bc_coef = nullptr;
+  int32_t* bct = nullptr;
+  double2* bct_coef = nullptr;
   double* kappa = nullptr;  // [4][M] detector factor per wall and slot
   double* det_w = nullptr;  // [Nd][4][npos] detector weights
   // beams: per beam spatial (boundary position) and angular (slot) factors, temporal samples
