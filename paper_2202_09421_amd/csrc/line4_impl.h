@@ -82,7 +82,7 @@ constexpr int inner_n2(int n1, int m) {
   switch (n1 * m) {
     case 216: case 675: case 810: return 3;
     case 48: case 64: case 96: case 128: case 640: case 768: case 960: case 1024: case 1152: return 4;
-    case 75: case 100: case 125: case 250: case 750: case 800: case 1125: return 5;
+    case 75: case 100: case 125: case 250: case 750: case 1125: return 5;
     case 90: case 162: case 288: case 324: case 432: case 486: case 648: case 972: case 1080: return 6;
     case 320: case 384: case 512: return 8;
     case 243: case 360: case 405: case 540: return 9;
@@ -109,7 +109,7 @@ constexpr int lines_per_wave(int n1, int m) {
     case 120: case 135: case 144: case 150: case 160: case 180: case 192: case 200: case 225: case 240:
     case 256: return 4;
     case 90: case 96: case 100: case 125: case 128: case 162: case 216: case 243: case 250: case 270: case 300:
-    case 375: case 576: case 625: case 729: return 2;
+    case 375: case 576: case 625: case 729: case 800: return 2;
     default: return 1;
   }
 }
@@ -525,25 +525,35 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
     stage_b<G, 1>(L, lane, tw);
     wave_order();
   }
+  // fold of the extension region onto the 2d matching points (transpose of the
+  // continuation): quad c sums column c over the extension rows.  From 128 to
+  // 600 points its first 8 coefficients are read before the last stage (N = 540:
+  // 437 us against 451, N = 160: 8.9 against 9.3; N = 90 and 1080 lose 4 and 1 %).
+  const int c = lane >> 2, part = lane & 3;
+  const bool on = c < 2 * dd;
+  constexpr int kFold = N >= 128 && N <= 600 ? 8 : 0;
+  double mf[kFold + 1];
+  if constexpr (ADJ) {
+#pragma unroll
+    for (int j = 0; j < kFold; ++j) mf[j] = D.Mx[min(part + 4 * j, CE - 1) * 2 * dd + min(c, 2 * dd - 1)];
+  }
   stage_a<G, 1>(L, lane, tw);
   wave_order();
   if constexpr (ADJ) {
-    // fold the extension region back onto the 2d matching points (transpose
-    // of the continuation): quad c sums column c over the extension rows
-    const int c = lane >> 2, part = lane & 3;
-    const bool on = c < 2 * dd;
     double sr[LPW] = {}, si[LPW] = {};
-    if (on) {
-#pragma unroll 4
-      for (int p = part; p < CE; p += 4) {
-        const double mv = D.Mx[p * 2 * dd + c];
-        const cx<double>* y = L + G::pos(n + p);
+    auto add = [&](int p, double mv) {
+      const cx<double>* y = L + G::pos(n + p);
 #pragma unroll
-        for (int l = 0; l < LPW; ++l) {
-          sr[l] += mv * y[l * G::LSZ].re;
-          si[l] += mv * y[l * G::LSZ].im;
-        }
+      for (int l = 0; l < LPW; ++l) {
+        sr[l] += mv * y[l * G::LSZ].re;
+        si[l] += mv * y[l * G::LSZ].im;
       }
+    };
+    if (on) {
+#pragma unroll
+      for (int j = 0; j < kFold; ++j)
+        if (part + 4 * j < CE) add(part + 4 * j, mf[j]);
+      for (int p = part + 4 * kFold; p < CE; p += 4) add(p, D.Mx[p * 2 * dd + c]);
     }
     cx<double>* q = L + (on ? G::pos(c < dd ? n - dd + c : 2 * dd - 1 - c) : 0);
 #pragma unroll

@@ -66,7 +66,7 @@ bool fourstep_split(int Np, int* n1, int* n2) {
     case 729: *n1 = 27; *n2 = 27; return true;
     case 750: *n1 = 10; *n2 = 75; return true;
     case 768: *n1 = 12; *n2 = 64; return true;
-    case 800: *n1 = 10; *n2 = 80; return true;
+    case 800: *n1 = 32; *n2 = 25; return true;
     case 810: *n1 = 18; *n2 = 45; return true;
     case 864: *n1 = 6; *n2 = 144; return true;
     case 900: *n1 = 4; *n2 = 225; return true;

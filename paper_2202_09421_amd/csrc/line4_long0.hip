@@ -15,7 +15,7 @@ static hipError_t longs(const Lines4Args<T>& a, int Np, int nq, bool adj, hipStr
     case 729: return adj ? go_one<T, true, 27, 27>(a, nq, s) : go_one<T, false, 27, 27>(a, nq, s);
     case 750: return adj ? go_one<T, true, 10, 75>(a, nq, s) : go_one<T, false, 10, 75>(a, nq, s);
     case 768: return adj ? go_one<T, true, 12, 64>(a, nq, s) : go_one<T, false, 12, 64>(a, nq, s);
-    case 800: return adj ? go_one<T, true, 10, 80>(a, nq, s) : go_one<T, false, 10, 80>(a, nq, s);
+    case 800: return adj ? go_one<T, true, 32, 25>(a, nq, s) : go_one<T, false, 32, 25>(a, nq, s);
     case 810: return adj ? go_one<T, true, 18, 45>(a, nq, s) : go_one<T, false, 18, 45>(a, nq, s);
     case 864: return adj ? go_one<T, true, 6, 144>(a, nq, s) : go_one<T, false, 6, 144>(a, nq, s);
     default: return hipErrorNotSupported;
