@@ -89,15 +89,38 @@ static bool smooth5(int64_t n) {
 }
 
 // ---------------------------------------------------------------- device upload helper
-template <typename V>
-static bool upload(const std::vector<V>& h, V** d) {
-  if (h.empty()) {
+// All tables of a plan in one device allocation, filled by one copy (an
+// allocation and a copy per table took most of the time of rte_plan_create on
+// small grids).  Tables start at multiples of 256 bytes.
+class TableUpload {
+ public:
+  template <typename V>
+  void add(const std::vector<V>& h, V** d) {
     *d = nullptr;
+    if (h.empty()) return;
+    const size_t off = (host_.size() + 255) & ~size_t(255), n = h.size() * sizeof(V);
+    host_.resize(off + n);
+    std::memcpy(host_.data() + off, h.data(), n);
+    slots_.push_back({reinterpret_cast<void**>(d), off});
+  }
+  bool commit(void** base) {
+    if (hipMalloc(base, host_.size()) != hipSuccess) {
+      *base = nullptr;
+      return false;
+    }
+    if (hipMemcpy(*base, host_.data(), host_.size(), hipMemcpyHostToDevice) != hipSuccess) return false;
+    for (const Slot& s : slots_) *s.ptr = static_cast<char*>(*base) + s.off;
     return true;
   }
-  if (hipMalloc((void**)d, h.size() * sizeof(V)) != hipSuccess) return false;
-  return hipMemcpy(*d, h.data(), h.size() * sizeof(V), hipMemcpyHostToDevice) == hipSuccess;
-}
+
+ private:
+  struct Slot {
+    void** ptr;
+    size_t off;
+  };
+  std::vector<char> host_;
+  std::vector<Slot> slots_;
+};
 
 // ---------------------------------------------------------------- FC plan for one direction
 static bool build_fc(const rte_problem& pb, int n, double h, std::vector<double>& buf, FcPlanDev& fc,
@@ -274,10 +297,7 @@ static bool validate(const rte_problem* p, const rte_beam* beams, int64_t nbm, c
 }
 
 static void free_tables(DeviceTables& t) {
-  void* ps[] = {t.xi, t.eta, t.Wt, t.bc, t.bc_coef, t.bct, t.bct_coef, t.kappa, t.det_w, t.beam_sp, t.beam_an, t.beam_tt, t.beam_off,
-                t.slot_m, t.fc_buf, t.det_sp, t.slot_rev, t.guard_flag};
-  for (void* p : ps)
-    if (p) (void)hipFree(p);
+  if (t.base) (void)hipFree(t.base);
   t = DeviceTables();
 }
 
@@ -546,13 +566,26 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
     btc[k] = bct[k].is_target | bct[k].ntgt << 1 | (bct[k].tgt[0] & 3) << 3 | (bct[k].tgt[1] & 3) << 5;
     btf[k] = make_double2(bct[k].coef[0], bct[k].coef[1]);
   }
-  bool ok = upload(xi, &p.dev.xi) && upload(eta, &p.dev.eta) && upload(Wt, &p.dev.Wt) && upload(bcc, &p.dev.bc) &&
-            upload(bcf, &p.dev.bc_coef) && upload(btc, &p.dev.bct) && upload(btf, &p.dev.bct_coef) && upload(kappa, &p.dev.kappa) && upload(detw, &p.dev.det_w) &&
-            upload(bsp, &p.dev.beam_sp) && upload(ban, &p.dev.beam_an) && upload(btt, &p.dev.beam_tt) &&
-            upload(boff, &p.dev.beam_off) && upload(slotm, &p.dev.slot_m) && upload(fcbuf, &p.dev.fc_buf) &&
-            upload(detsp, &p.dev.det_sp) && upload(srev, &p.dev.slot_rev) &&
-            upload(std::vector<unsigned long long>(1, 0ull), &p.dev.guard_flag);
-  if (!ok) {
+  TableUpload up;
+  up.add(xi, &p.dev.xi);
+  up.add(eta, &p.dev.eta);
+  up.add(Wt, &p.dev.Wt);
+  up.add(bcc, &p.dev.bc);
+  up.add(bcf, &p.dev.bc_coef);
+  up.add(btc, &p.dev.bct);
+  up.add(btf, &p.dev.bct_coef);
+  up.add(kappa, &p.dev.kappa);
+  up.add(detw, &p.dev.det_w);
+  up.add(bsp, &p.dev.beam_sp);
+  up.add(ban, &p.dev.beam_an);
+  up.add(btt, &p.dev.beam_tt);
+  up.add(boff, &p.dev.beam_off);
+  up.add(slotm, &p.dev.slot_m);
+  up.add(fcbuf, &p.dev.fc_buf);
+  up.add(detsp, &p.dev.det_sp);
+  up.add(srev, &p.dev.slot_rev);
+  up.add(std::vector<unsigned long long>(1, 0ull), &p.dev.guard_flag);
+  if (!up.commit(&p.dev.base)) {
     set_error("device allocation or upload of the plan tables failed");
     free_tables(p.dev);
     delete P;

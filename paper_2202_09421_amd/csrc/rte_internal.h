@@ -76,6 +76,7 @@ struct BcRuleT {
 };
 
 struct DeviceTables {
+  void* base = nullptr;     // the one allocation that holds every table
   // ordinates in storage order (slot s = 4*g + r)
   double* xi = nullptr;     // [M]
   double* eta = nullptr;    // [M]
