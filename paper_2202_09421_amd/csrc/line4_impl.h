@@ -508,7 +508,7 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
     // matching values): job (row p, line l)
     for (int e = lane; e < LPW * CE; e += 64) {
       const int l = e % LPW, p = e / LPW;
-      if (LPW > 1 && e >= 64) row.load(D, dd, p);
+      if (e >= 64) row.load(D, dd, p);
       L[l * G::LSZ + G::pos(n + p)] = row.apply(D, dd, L + l * G::LSZ);
     }
   }
