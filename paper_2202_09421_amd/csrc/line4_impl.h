@@ -52,7 +52,7 @@ struct Lines4Dir {
   int n, CE;               // nodes per line, extension points
   int pr[kMaxFcD], pl[kMaxFcD];  // LDS positions of the matching values n - d + k and d - 1 - k (k < d; else 0)
   int nlines, npe;         // lines, line pairs rounded up to even
-  int64_t line_stride, pt_stride;
+  bool along_x;            // lines are rows (else columns)
 };
 
 template <typename T>
@@ -61,6 +61,7 @@ struct Lines4Args {
   T* out[2];
   Lines4Dir dir[2];
   const double2* tw;       // twiddle powers in job order (line4_orders)
+  RowMap rows;
   int64_t grp_stride, inst_stride;
   int G, d;
   int first, units_first;  // direction of units [0, units_first) of a (source, group)
@@ -416,10 +417,16 @@ struct MxRow {
   }
 };
 
+// byte offset of point i of a line
+struct PtMap {
+  uint32_t inv, ps, skip;
+  __device__ __forceinline__ uint32_t operator()(int i) const { return (uint32_t)i * ps + __umulhi((uint32_t)i, inv) * skip; }
+};
+
 // Stores of one lane: its piece of every PT-th point.  NT: non-temporal, for
 // plans that stream their state arrays.
 template <class G, typename T, bool NT>
-__device__ __forceinline__ void store_unit(char* out, const double* src, uint32_t lout, uint32_t ps, int i0, int n) {
+__device__ __forceinline__ void store_unit(char* out, const double* src, uint32_t lout, PtMap pt, int i0, int n) {
   constexpr int SL = 16 / sizeof(T), PT = G::NTH / (8 / SL), TMAX = (G::N - 1 + PT - 1) / PT;
   typedef typename Vec16<T>::type V16;
 #pragma unroll
@@ -430,7 +437,7 @@ __device__ __forceinline__ void store_unit(char* out, const double* src, uint32_
       V16 o;
 #pragma unroll
       for (int r = 0; r < SL; ++r) o[r] = T(q[2 * r * G::LSZ]);
-      V16* dst = reinterpret_cast<V16*>(out + (lout + (uint32_t)i * ps));
+      V16* dst = reinterpret_cast<V16*>(out + (lout + pt(i)));
       if constexpr (NT) __builtin_nontemporal_store(o, dst);
       else *dst = o;
     }
@@ -455,7 +462,8 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
   if (line0 >= D.nlines) return;
   const bool has1 = line0 + 1 < D.nlines;
   const int g = (int)blockIdx.y, s0 = g * kGroup;
-  const int64_t base = (int64_t)blockIdx.z * a.inst_stride + (int64_t)g * a.grp_stride + (int64_t)line0 * D.line_stride;
+  const int64_t l0 = D.along_x ? a.rows(line0) : line0 * kGroup;
+  const int64_t base = (int64_t)blockIdx.z * a.inst_stride + (int64_t)g * a.grp_stride + l0;
   const int n = D.n, CE = D.CE, dd = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // lane = (point, line, 16-byte piece of its 4 slots): neighbouring lanes
@@ -468,7 +476,9 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
 
   // byte offsets from the unit's base fit 32 bits (one source's state is below 4 GiB)
   const char* in = reinterpret_cast<const char*>(a.in + base);
-  const uint32_t ls = (uint32_t)(D.line_stride * sizeof(T)), ps = (uint32_t)(D.pt_stride * sizeof(T));
+  const uint32_t ls = (uint32_t)(((D.along_x ? a.rows(line0 + 1) : (line0 + 1) * kGroup) - l0) * sizeof(T));
+  const PtMap pt{a.rows.inv, (uint32_t)((D.along_x ? kGroup : a.rows.row) * sizeof(T)),
+                 D.along_x ? 0u : (uint32_t)(a.rows.skip * sizeof(T))};
   const uint32_t lin = ((it && has1) ? ls : 0u) + 16u * pc;
   constexpr int CH = TMAX < 20 ? TMAX : (TMAX + 1) / 2;
   // the lane's row of the continuation matrix (first job of the extension)
@@ -481,7 +491,7 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
 #pragma unroll
     for (int t = 0; t < CH; ++t) {
       const int i = i0 + PT * (c0 + t);
-      if (c0 + t < TMAX) v[t] = *reinterpret_cast<const V16*>(in + (lin + (uint32_t)min(i, n - 1) * ps));
+      if (c0 + t < TMAX) v[t] = *reinterpret_cast<const V16*>(in + (lin + pt(min(i, n - 1))));
     }
     if (!has1 && it) {
 #pragma unroll
@@ -571,8 +581,8 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
   const uint32_t lout = (it ? ls : 0u) + 16u * pc;
   char* out = reinterpret_cast<char*>(a.out[dirn] + base);
   const double* src = bufd + 2 * (pc * SL * G::LSZ) + it;
-  if (a.nt_out) store_unit<G, T, true>(out, src, lout, ps, i0, n);
-  else store_unit<G, T, false>(out, src, lout, ps, i0, n);
+  if (a.nt_out) store_unit<G, T, true>(out, src, lout, pt, i0, n);
+  else store_unit<G, T, false>(out, src, lout, pt, i0, n);
 }
 
 constexpr size_t kLines4MaxLds = 160 * 1024;

@@ -151,13 +151,13 @@ static hipError_t launch4_t(const Plan& p, const LineLaunch& L, hipStream_t s) {
     D.nlines = (int)(k ? p.nx : p.ny);
     const int np = (D.nlines + 1) / 2;
     D.npe = np + (np & 1);
-    D.line_stride = k ? kGroup : p.nxp * kGroup;
-    D.pt_stride = k ? p.nxp * kGroup : kGroup;
+    D.along_x = k == 0;
   }
   const bool dx = (L.dirs & 1) != 0, dy = (L.dirs & 2) != 0;
   const FcPlanDev& fc = dx ? p.fcx : p.fcy;
   a.tw = reinterpret_cast<const double2*>(fc.tw4);
   a.d = fc.d;
+  a.rows = p.rows;
   a.grp_stride = p.grp_stride;
   a.inst_stride = p.inst_stride;
   a.G = (int)p.G;

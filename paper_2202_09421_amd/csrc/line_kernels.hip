@@ -2,10 +2,10 @@
 // derivative along x lines (rows) or y lines (columns), and its exact
 // transpose for the adjoint (Sec. 4.3; Algorithm 1, loops over y_j and x_i).
 //
-// Storage: a state is [q][g][j][i][r] with g = ordinate group (4 slots),
-// r = slot within the group and rows padded to nxp nodes, so a row of one
-// group is contiguous and a column of one group is a run of 32-byte (FP64)
-// chunks.  This generic kernel (any 5-smooth N_p, runtime Stockham passes)
+// Storage: a state is [q][band of rows][g][row][i][r] with g = ordinate group
+// (4 slots), r = slot within the group and rows padded to nxp nodes, so a row
+// of one group is contiguous and a column of one group is a run of 32-byte
+// (FP64) chunks.  This generic kernel (any 5-smooth N_p, runtime Stockham passes)
 // serves the lengths without a four-step split.  One workgroup handles one
 // (line, group, source): the 4 slots form two complex lines (slots r0 + i r1
 // and r2 + i r3), differentiated together since the FC operator is
@@ -30,7 +30,9 @@ struct LineArgs {
   const double* coef;  // xi or eta per slot
   FcPlanDev fc;
   int nlines;
-  int64_t line_stride, pt_stride, grp_stride, inst_stride;
+  bool along_x;
+  RowMap rows;
+  int64_t grp_stride, inst_stride;
 };
 
 // XCD-aware line index: the 8 XCDs receive blocks round-robin, so block b
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(LineArgs<T> a) {
   // reach |A| ~ 5e3, so in FP32 it would lose ~4 digits
   cplx<double>* cs = reinterpret_cast<cplx<double>*>(bufB + 2 * Np);
 
-  const int64_t base = (int64_t)q * a.inst_stride + (int64_t)g * a.grp_stride + (int64_t)line * a.line_stride;
+  const int64_t base = (int64_t)q * a.inst_stride + (int64_t)g * a.grp_stride + (a.along_x ? a.rows(line) : line * kGroup);
   const T* in = a.in + base;
   const int s0 = g * kGroup;
 
@@ -74,7 +76,7 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(LineArgs<T> a) {
 
   // ---- load the line (4 slots per point) into two complex lines
   for (int i = tid; i < n; i += nthr) {
-    const T* p = in + (int64_t)i * a.pt_stride;
+    const T* p = in + (a.along_x ? i * kGroup : a.rows(i));
     const CT v0 = p[0], v1 = p[1], v2 = p[2], v3 = p[3];
     bufA[i] = {v0 * cf[0], v1 * cf[1]};
     bufA[Np + i] = {v2 * cf[2], v3 * cf[3]};
@@ -212,7 +214,7 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(LineArgs<T> a) {
         dv[3] += gs[(1 * 2 + 0) * kMaxFcD + k].im;
       }
     }
-    const int64_t off = (int64_t)i * a.pt_stride;
+    const int64_t off = a.along_x ? i * kGroup : a.rows(i);
 #pragma unroll
     for (int r = 0; r < 4; ++r) out[off + r] = T(c4[r] * dv[r]);
   }
@@ -225,16 +227,14 @@ static hipError_t launch_mode(const Plan& p, const void* in, void* out, int dir,
   a.out = static_cast<T*>(out);
   a.coef = (dir == 0) ? p.dev.xi : p.dev.eta;
   a.fc = (dir == 0) ? p.fcx : p.fcy;
+  a.along_x = dir == 0;
+  a.rows = p.rows;
   a.grp_stride = p.grp_stride;
   a.inst_stride = p.inst_stride;
   if (dir == 0) {
     a.nlines = (int)p.ny;
-    a.line_stride = p.nxp * kGroup;
-    a.pt_stride = kGroup;
   } else {
     a.nlines = (int)p.nx;
-    a.line_stride = kGroup;
-    a.pt_stride = p.nxp * kGroup;
   }
   const int Np = a.fc.Np;
   const size_t shmem = line_shmem_bytes(Np, p.dtype);

@@ -77,6 +77,7 @@ struct NodeGeom {
   int nx, ny, nxp, M, Mpad, G, nb, npos, K1, RT, NT, npos_total;
   int q0;                   // first source of the chunk (blockIdx.y is the source within it)
   int ntiles, tile_shift;   // tiles are visited from the one holding the last row's start
+  RowMap rows;
   int64_t grp_stride, inst_stride;
 };
 
@@ -206,7 +207,7 @@ __device__ __forceinline__ void lane_offsets(const NodeGeom& G, const TileLane& 
   for (int v = 0; v < 4; ++v) {
     const int s = lane_slot<T>(t, v);
     ok[v] = t.valid && (s >> 2) < G.G;
-    off[v] = (uint32_t)(((uint32_t)(s >> 2) * (uint32_t)G.grp_stride + (uint32_t)t.P * kGroup + (s & 3)) * sizeof(T));
+    off[v] = (uint32_t)(((uint32_t)(s >> 2) * (uint32_t)G.grp_stride + (uint32_t)G.rows(t.j) + (uint32_t)t.i * kGroup + (s & 3)) * sizeof(T));
   }
 }
 // Byte offset of the value at the reversed ordinate of the lane's value v
@@ -214,7 +215,7 @@ __device__ __forceinline__ void lane_offsets(const NodeGeom& G, const TileLane& 
 template <typename T>
 __device__ __forceinline__ uint32_t pair_offset(const NodeGeom& G, const TileLane& t, const int32_t* slot_rev, int v) {
   const int sr = slot_rev[lane_slot<T>(t, v)];
-  return (uint32_t)(((uint32_t)(sr >> 2) * (uint32_t)G.grp_stride + (uint32_t)t.P * kGroup + (sr & 3)) * sizeof(T));
+  return (uint32_t)(((uint32_t)(sr >> 2) * (uint32_t)G.grp_stride + (uint32_t)G.rows(t.j) + (uint32_t)t.i * kGroup + (sr & 3)) * sizeof(T));
 }
 // Value of slot c (0..3) of the group that holds the lane's value v, for the
 // same node: another lane's register (FP64) or one of the lane's own (FP32).
@@ -686,6 +687,7 @@ static NodeGeom make_geom(const Plan& p) {
   g.q0 = (int)p.cq0;
   g.ntiles = (g.npos_total + 15) / 16;
   g.tile_shift = (int)((p.ny - 1) * p.nxp / 16);
+  g.rows = p.rows;
   g.grp_stride = p.grp_stride;
   g.inst_stride = p.inst_stride;
   return g;
@@ -929,7 +931,7 @@ __global__ void grad_reduce_kernel(const double* __restrict__ ga, const double* 
 
 template <typename T>
 __global__ void unpermute_kernel(const T* __restrict__ st, T* __restrict__ out, const int32_t* __restrict__ slot_m,
-                                 int M, int nx, int nxp, int64_t Nn, int Nq, int64_t grp_stride, int64_t inst_stride) {
+                                 int M, int nx, RowMap rows, int64_t Nn, int Nq, int64_t grp_stride, int64_t inst_stride) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t total = (int64_t)Nq * Nn * M;
   if (t >= total) return;
@@ -938,13 +940,13 @@ __global__ void unpermute_kernel(const T* __restrict__ st, T* __restrict__ out, 
   const int q = (int)(t / (M * Nn));
   const int g = s / kGroup, r = s % kGroup;
   const int64_t j = gn / nx, i = gn - j * nx;
-  const T v = st[(int64_t)q * inst_stride + (int64_t)g * grp_stride + (j * nxp + i) * kGroup + r];
+  const T v = st[(int64_t)q * inst_stride + (int64_t)g * grp_stride + rows((int)j) + i * kGroup + r];
   out[((int64_t)q * Nn + gn) * M + slot_m[s]] = v;
 }
 
 template <typename T>
 __global__ void permute_kernel(const T* __restrict__ in, T* __restrict__ st, const int32_t* __restrict__ slot_m, int M,
-                               int nx, int nxp, int64_t Nn, int Nq, int64_t grp_stride, int64_t inst_stride) {
+                               int nx, RowMap rows, int64_t Nn, int Nq, int64_t grp_stride, int64_t inst_stride) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t total = (int64_t)Nq * Nn * M;
   if (t >= total) return;
@@ -953,7 +955,7 @@ __global__ void permute_kernel(const T* __restrict__ in, T* __restrict__ st, con
   const int q = (int)(t / (M * Nn));
   const int g = s / kGroup, r = s % kGroup;
   const int64_t j = gn / nx, i = gn - j * nx;
-  st[(int64_t)q * inst_stride + (int64_t)g * grp_stride + (j * nxp + i) * kGroup + r] = in[((int64_t)q * Nn + gn) * M + slot_m[s]];
+  st[(int64_t)q * inst_stride + (int64_t)g * grp_stride + rows((int)j) + i * kGroup + r] = in[((int64_t)q * Nn + gn) * M + slot_m[s]];
 }
 
 // Scalar flux of a state, eq. (photondensity) with the trapezoid rule on the
@@ -962,12 +964,12 @@ __global__ void permute_kernel(const T* __restrict__ in, T* __restrict__ st, con
 // FP64 in slot order.  Grid: x over nodes of a row, y over rows, z over the
 // chunk's sources.
 template <typename T>
-__global__ void flux_map_kernel(const T* __restrict__ st, double* __restrict__ out, int M, int nx, int nxp,
+__global__ void flux_map_kernel(const T* __restrict__ st, double* __restrict__ out, int M, int nx, RowMap rows,
                                 int64_t grp_stride, int64_t inst_stride, int64_t out_q_stride, double dth) {
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= nx) return;
   const int j = (int)blockIdx.y, q = (int)blockIdx.z;
-  const T* p = st + (int64_t)q * inst_stride + ((int64_t)j * nxp + i) * kGroup;
+  const T* p = st + (int64_t)q * inst_stride + rows(j) + (int64_t)i * kGroup;
   double acc = 0.0;
   for (int s = 0; s < M; ++s) acc += (double)p[(int64_t)(s / kGroup) * grp_stride + s % kGroup];
   out[(int64_t)q * out_q_stride + (int64_t)j * nx + i] = dth * acc;
@@ -1048,10 +1050,10 @@ hipError_t launch_permute(const Plan& p, const void* in, void* state, hipStream_
   const dim3 grid((unsigned)((total + 255) / 256));
   if (p.dtype == RTE_F64)
     hipLaunchKernelGGL(permute_kernel<double>, grid, dim3(256), 0, s, (const double*)in, (double*)state, p.dev.slot_m,
-                       (int)p.M, (int)p.nx, (int)p.nxp, Nn, (int)p.cnq, p.grp_stride, p.inst_stride);
+                       (int)p.M, (int)p.nx, p.rows, Nn, (int)p.cnq, p.grp_stride, p.inst_stride);
   else
     hipLaunchKernelGGL(permute_kernel<float>, grid, dim3(256), 0, s, (const float*)in, (float*)state, p.dev.slot_m,
-                       (int)p.M, (int)p.nx, (int)p.nxp, Nn, (int)p.cnq, p.grp_stride, p.inst_stride);
+                       (int)p.M, (int)p.nx, p.rows, Nn, (int)p.cnq, p.grp_stride, p.inst_stride);
   return hipGetLastError();
 }
 
@@ -1061,10 +1063,10 @@ hipError_t launch_flux_map(const Plan& p, const void* state, double* out, int64_
   const double dth = 6.283185307179586476925 / (double)p.M;  // 2 pi / M
   if (p.dtype == RTE_F64)
     hipLaunchKernelGGL(flux_map_kernel<double>, grid, dim3(256), 0, s, (const double*)state, out, (int)p.M,
-                       (int)p.nx, (int)p.nxp, p.grp_stride, p.inst_stride, out_q_stride, dth);
+                       (int)p.nx, p.rows, p.grp_stride, p.inst_stride, out_q_stride, dth);
   else
     hipLaunchKernelGGL(flux_map_kernel<float>, grid, dim3(256), 0, s, (const float*)state, out, (int)p.M,
-                       (int)p.nx, (int)p.nxp, p.grp_stride, p.inst_stride, out_q_stride, dth);
+                       (int)p.nx, p.rows, p.grp_stride, p.inst_stride, out_q_stride, dth);
   return hipGetLastError();
 }
 
@@ -1076,10 +1078,10 @@ hipError_t launch_unpermute(const Plan& p, const void* state, void* out, hipStre
   const int64_t off = p.cq0 * Nn * p.M;
   if (p.dtype == RTE_F64)
     hipLaunchKernelGGL(unpermute_kernel<double>, grid, dim3(256), 0, s, (const double*)state, (double*)out + off,
-                       p.dev.slot_m, (int)p.M, (int)p.nx, (int)p.nxp, Nn, (int)p.cnq, p.grp_stride, p.inst_stride);
+                       p.dev.slot_m, (int)p.M, (int)p.nx, p.rows, Nn, (int)p.cnq, p.grp_stride, p.inst_stride);
   else
     hipLaunchKernelGGL(unpermute_kernel<float>, grid, dim3(256), 0, s, (const float*)state, (float*)out + off,
-                       p.dev.slot_m, (int)p.M, (int)p.nx, (int)p.nxp, Nn, (int)p.cnq, p.grp_stride, p.inst_stride);
+                       p.dev.slot_m, (int)p.M, (int)p.nx, p.rows, Nn, (int)p.cnq, p.grp_stride, p.inst_stride);
   return hipGetLastError();
 }
 

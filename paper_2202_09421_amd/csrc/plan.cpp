@@ -302,6 +302,37 @@ static void free_tables(DeviceTables& t) {
   t = DeviceTables();
 }
 
+// Rows of a band of the state layout.  A node pass reads a node of every group
+// from up to eight arrays, a y line every row of one group.  With a whole
+// plane per group (one band) the node passes met the same memory channels
+// again and again at some plane sizes; with one row per band they do not, but
+// the rows of a y line are then G pitches apart.  Bands of 11-21 rows serve
+// both, odd ones only: a power-of-two step between bands brings the clashes
+// back.  Both line and both node passes together, M = 64, us, planes / 1 row /
+// 16 rows / 15 rows: 513 x 513 x 4 sources FP64 2690 / 2717 / 2572 / 2536,
+// 1025 x 1025 FP32 2092 / 2179 / 2138 / 1889, 1025 x 1025 FP64 2672 / 2661 /
+// 2608 / 2560, 513 x 513 x 4 FP32 1657 / 1748 / 1651 / 1663; at 257 nodes and
+// below all are within 3 %.  15 rows, or the height of those measured good at
+// ten sizes that pads fewer, where 15 would pad more than a 32nd.
+static int64_t band_rows(int64_t ny) {
+  int64_t best = 0, pad = 0;
+  for (int64_t b : {15, 13, 17, 19, 11}) {
+    const int64_t q = (b - ny % b) % b;
+    if (best == 0 || (pad * 32 > ny && q < pad)) best = b, pad = q;
+  }
+  return std::min(best, ny);
+}
+
+static void set_bands(Plan& p, int64_t band) {
+  p.rows.band = (int)band;
+  p.rows.inv = (uint32_t)((int64_t(1) << 32) / band + 1);
+  p.rows.row = p.nxp * kGroup;
+  p.grp_stride = band * p.rows.row;
+  const int64_t band_stride = p.G * p.grp_stride;
+  p.rows.skip = band_stride - p.grp_stride;
+  p.inst_stride = (p.ny + band - 1) / band * band_stride;
+}
+
 int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams, const rte_detector* dets,
                 int64_t n_det, rte_plan** out) {
   if (!out) {
@@ -342,9 +373,10 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
     const int64_t pitch = p.nxp * kGroup * (prob->dtype == RTE_F64 ? 8 : 4);
     if (pitch % 2048 == 0) p.nxp += align;
   }
-  p.grp_stride = p.ny * p.nxp * kGroup;
-  p.inst_stride = p.G * p.grp_stride;
-  if (p.inst_stride * (prob->dtype == RTE_F64 ? 8 : 4) >= (int64_t(1) << 32)) {
+  const int64_t es = (prob->dtype == RTE_F64) ? 8 : 4, limit = (int64_t(1) << 32) / es;
+  set_bands(p, band_rows(p.ny));
+  if (p.inst_stride >= limit) set_bands(p, p.ny);  // no padded rows
+  if (p.inst_stride >= limit) {
     set_error("one source's state exceeds 4 GiB (ordinates x nodes too large)");
     delete P;
     return RTE_EUNSUPPORTED;
@@ -361,8 +393,8 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   p.chunk = (prob->combo_chunk > 0) ? std::min<int64_t>(prob->combo_chunk, p.Nq) : p.Nq;
   p.cq0 = 0;
   p.cnq = p.chunk;
-  p.stream_nt = p.chunk * p.inst_stride * (prob->dtype == RTE_F64 ? 8 : 4) > kStreamNtBytes;
-  p.line_nt = p.chunk * p.inst_stride * (prob->dtype == RTE_F64 ? 8 : 4) > kLineNtBytes;
+  p.stream_nt = p.chunk * p.inst_stride * es > kStreamNtBytes;
+  p.line_nt = p.chunk * p.inst_stride * es > kLineNtBytes;
   const int M = (int)p.M;
   const double dx = (prob->xmax - prob->xmin) / prob->Nx;
   const double dy = (prob->ymax - prob->ymin) / prob->Ny;

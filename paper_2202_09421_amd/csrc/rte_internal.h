@@ -105,15 +105,27 @@ struct DeviceTables {
   unsigned long long* guard_flag = nullptr;
 };
 
+// Offset of row j of a state: rows come in bands, and a band holds its rows of
+// every ordinate group, [band][g][row][i][r].  Strides in elements.
+struct RowMap {
+  uint32_t inv = 0;          // floor(2^32 / band) + 1: j / band = mulhi(j, inv) for j * band < 2^32
+  int band = 0;
+  int64_t row = 0;           // between rows of a band
+  int64_t skip = 0;          // between bands, less band rows
+#ifdef __HIPCC__
+  __device__ __forceinline__ int64_t operator()(int j) const { return j * row + __umulhi((uint32_t)j, inv) * skip; }
+#endif
+};
+
 struct Plan {
   rte_problem prob{};
   int dtype = RTE_F64;
   int64_t nx = 0, ny = 0, M = 0, G = 0, Mpad = 0, K = 0, Nq = 0, Nd = 0, nbeams = 0;
-  // state layout [q][g][j][i][r]: rows padded to nxp nodes so that every row
-  // starts on a 128-byte boundary (4 FP64 or 8 FP32 nodes of one group)
+  // state layout [q][band][g][row of the band][i][r]: rows padded to nxp nodes so that
+  // every row starts on a 128-byte boundary (4 FP64 or 8 FP32 nodes of one group)
   int64_t nxp = 0;
-  int64_t grp_stride = 0;   // ny * nxp * kGroup elements
-  int64_t inst_stride = 0;  // G * grp_stride
+  RowMap rows;
+  int64_t grp_stride = 0, inst_stride = 0;  // elements between groups (of a band) and sources
   rte_schedule sched{1, 0, 0, 2, 1, 0};  // launch schedule (node_tiles_per_block resolved at create)
   int64_t sched_version = 0;       // bumped by every schedule change (graph keys)
   int64_t nb = 0;     // boundary nodes 2(nx+ny)-4
