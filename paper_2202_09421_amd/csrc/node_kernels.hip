@@ -127,20 +127,57 @@ __device__ __forceinline__ TileLane tile_lane(const NodeGeom& G) {
   return t;
 }
 
+// A operand of 4 MFMA steps (input slots 16 k .. 16 k + 15) of the wave's row
+// tile.  Wf holds them per lane in the plan's type, so they come in 16-byte
+// pieces; as rows of the FP64 matrix they took 16 loads of 8 bytes per 64
+// slots, in FP32 more bytes than the wave's states (forward / adjoint pass, us,
+// before and now: 513 x 513 x 64, 4 sources, FP32 405 / 501 -> 363 / 460, FP64
+// 752 / 842 -> 735 / 827; 400 x 400 x 72 FP64 168 / 216 -> 145 / 182).
+template <typename T>
+__device__ __forceinline__ void load_wf(T* w, const T* __restrict__ Wf, const NodeGeom& G, const TileLane& t, int k) {
+  constexpr int V = 16 / sizeof(T);
+  typedef T vec __attribute__((ext_vector_type(V)));
+  const vec* p = reinterpret_cast<const vec*>(Wf) + (t.rt * G.RT + k) * (4 / V) * 64 + (threadIdx.x & 63);
+#pragma unroll
+  for (int h = 0; h < 4 / V; ++h) {
+    const vec x = p[64 * h];
+#pragma unroll
+    for (int v = 0; v < V; ++v) w[V * h + v] = x[v];
+  }
+}
+
 // MFMA product for the wave's row tile: B operand from the LDS tile Bs
-// ([Mpad][16] of this tile), A fragments af (preloaded) or read from Wt.
+// ([Mpad][16] of this tile), A fragments af
+// (preloaded) or, for RTC = 0, read one column tile ahead (FP32: 40 us against
+// 43 at 257 x 257 x 96) or when needed (FP64, where the registers of the read
+// ahead cost a wave: 400 x 400 x 72 145 us against 163; all in registers 159).
 template <typename T, int RTC>
-__device__ __forceinline__ typename Mfma<T>::acc_t scatter_tile(const T* Bs, const T* af, const double* __restrict__ Wt,
+__device__ __forceinline__ typename Mfma<T>::acc_t scatter_tile(const T* Bs, const T* af, const T* __restrict__ Wf,
                                                                const NodeGeom& G, const TileLane& t) {
   typedef typename Mfma<T>::acc_t acc_t;
   acc_t acc = {0, 0, 0, 0};
+  auto tile = [&](int k, const T* w) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = Mfma<T>::step(w[ks], Bs[(16 * k + 4 * ks + t.r) * 16 + t.node], acc);
+  };
   if constexpr (RTC > 0) {
 #pragma unroll
-    for (int ks = 0; ks < 4 * RTC; ++ks) acc = Mfma<T>::step(af[ks], Bs[(4 * ks + t.r) * 16 + t.node], acc);
+    for (int k = 0; k < RTC; ++k) tile(k, af + 4 * k);
+  } else if constexpr (kVecLane<T>) {
+    T w[4] = {af[0], af[1], af[2], af[3]};
+    for (int k = 0; k < G.RT; ++k) {
+      T next[4];
+      load_wf(next, Wf, G, t, min(k + 1, G.RT - 1));
+      tile(k, w);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) w[v] = next[v];
+    }
   } else {
-    const int col = 16 * t.rt + t.node;
-    for (int ks = 0; ks < 4 * G.RT; ++ks)
-      acc = Mfma<T>::step(T(Wt[(4 * ks + t.r) * G.Mpad + col]), Bs[(4 * ks + t.r) * 16 + t.node], acc);
+    for (int k = 0; k < G.RT; ++k) {
+      T w[4];
+      load_wf(w, Wf, G, t, k);
+      tile(k, w);
+    }
   }
   return acc;
 }
@@ -229,11 +266,10 @@ __device__ __forceinline__ T group_peer(const T* x, int v, int c, const TileLane
 }
 
 template <typename T, int RTC>
-__device__ __forceinline__ void load_afrag(T* af, const double* __restrict__ Wt, const NodeGeom& G, const TileLane& t) {
-  if constexpr (RTC > 0) {
-    const int col = 16 * t.rt + t.node;
+__device__ __forceinline__ void load_afrag(T* af, const T* __restrict__ Wf, const NodeGeom& G, const TileLane& t) {
+  if constexpr (RTC > 0 || kVecLane<T>) {
 #pragma unroll
-    for (int ks = 0; ks < 4 * RTC; ++ks) af[ks] = T(Wt[(4 * ks + t.r) * G.Mpad + col]);
+    for (int k = 0; k < (RTC > 0 ? RTC : 1); ++k) load_wf(af + 4 * k, Wf, G, t, k);
   }
 }
 
@@ -243,7 +279,7 @@ struct NodeFwdArgs {
   const T* u; const T* X; const T* Y; const T* L1; const T* L2; const T* L3;
   const T* mu_a; const T* mu_s;
   T* u_out; T* L_out; double* flux;
-  const double* Wt; const int32_t* bc; const double2* bc_coef; const double* kappa;
+  const T* Wf; const int32_t* bc; const double2* bc_coef; const double* kappa;
   const double* beam_sp; const double* beam_an; const double* beam_tt; const int32_t* beam_off;
   // continuous adjoint (CADJ): inflow source table, paired forward state,
   // reversed-ordinate slots, gradient maps, quadrature dtheta dx dy dt
@@ -331,14 +367,14 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_fwd_kernel(NodeFwd
   }
   const int gn = t.j * G.nx + t.i;
   const T A = t.valid ? a.mu_a[gn] : T(0), B = t.valid ? a.mu_s[gn] : T(0);
-  T af[RTC > 0 ? 4 * RTC : 1];
-  load_afrag<T, RTC>(af, a.Wt, G, t);
+  T af[RTC > 0 ? 4 * RTC : 4];
+  load_afrag<T, RTC>(af, a.Wf, G, t);
   const int b0 = a.beam_off[q], b1 = a.beam_off[q + 1];   // the source's beams
 
 #pragma unroll
   for (int v = 0; v < 4; ++v) Bs[lane_slot<T>(t, v) * 16 + t.node] = u[v];
   __syncthreads();
-  const typename Mfma<T>::acc_t S = scatter_tile<T, RTC>(Bs, af, a.Wt, G, t);
+  const typename Mfma<T>::acc_t S = scatter_tile<T, RTC>(Bs, af, a.Wf, G, t);
 
   // L^n (plus the volumetric source) and the AB4 combination
   const T cdt = T(a.cdt);
@@ -501,7 +537,7 @@ struct NodeAdjArgs {
   const T* v1; const T* v2; const T* v3; const T* u;
   const T* mu_a; const T* mu_s; const double* inj;
   double* ga; double* gb;
-  const double* Wt; const int32_t* bct; const double2* bct_coef; const double* kappa;
+  const T* Wf; const int32_t* bct; const double2* bct_coef; const double* kappa;
   NodeGeom geo;
   int step;
   double cdt;
@@ -554,8 +590,8 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_adj_kernel(NodeAdj
   }
   const int gn = t.j * G.nx + t.i;
   const T A = t.valid ? a.mu_a[gn] : T(0), B = t.valid ? a.mu_s[gn] : T(0);
-  T af[RTC > 0 ? 4 * RTC : 1];
-  load_afrag<T, RTC>(af, a.Wt, G, t);
+  T af[RTC > 0 ? 4 * RTC : 4];
+  load_afrag<T, RTC>(af, a.Wf, G, t);
   // the node's gradient-map entries, read with the state by the one lane
   // per node that updates them at the end (no load round trip after the
   // reduction); each (source, node) belongs to one block of the launch
@@ -570,7 +606,7 @@ __global__ __launch_bounds__(RTC == 0 ? 1024 : 512) void node_adj_kernel(NodeAdj
 #pragma unroll
   for (int v = 0; v < 4; ++v) Bs[lane_slot<T>(t, v) * 16 + t.node] = w[v];
   __syncthreads();
-  const typename Mfma<T>::acc_t S = scatter_tile<T, RTC>(Bs, af, a.Wt, G, t);
+  const typename Mfma<T>::acc_t S = scatter_tile<T, RTC>(Bs, af, a.Wf, G, t);
 
   // P1^n and ubar^n, the gradient products
   const double cdt = a.cdt;
@@ -746,7 +782,7 @@ static hipError_t node_fwd_t(const Plan& p, const NodeFwdLaunch& L, hipStream_t 
   a.L1 = (const T*)L.L1; a.L2 = (const T*)L.L2; a.L3 = (const T*)L.L3;
   a.mu_a = (const T*)L.mu_a; a.mu_s = (const T*)L.mu_s;
   a.u_out = (T*)L.u_out; a.L_out = (T*)L.L_out; a.flux = L.flux;
-  a.Wt = p.dev.Wt; a.bc = p.dev.bc; a.bc_coef = p.dev.bc_coef; a.kappa = p.dev.kappa;
+  a.Wf = (const T*)p.dev.Wf; a.bc = p.dev.bc; a.bc_coef = p.dev.bc_coef; a.kappa = p.dev.kappa;
   a.beam_sp = p.dev.beam_sp; a.beam_an = p.dev.beam_an; a.beam_tt = p.dev.beam_tt; a.beam_off = p.dev.beam_off;
   a.csrc = L.csrc; a.upair = (const T*)L.upair; a.slot_rev = p.dev.slot_rev; a.ga = L.ga; a.gb = L.gb;
   a.vsrc = L.vsrc ? *L.vsrc : rte_separable{0, 0, nullptr, nullptr, nullptr};
@@ -787,7 +823,7 @@ static hipError_t node_adj_t(const Plan& p, const NodeAdjLaunch& L, hipStream_t 
   a.v1 = (const T*)L.v1; a.v2 = (const T*)L.v2; a.v3 = (const T*)L.v3; a.u = (const T*)L.u;
   a.mu_a = (const T*)L.mu_a; a.mu_s = (const T*)L.mu_s; a.inj = L.inj;
   a.ga = L.ga; a.gb = L.gb;
-  a.Wt = p.dev.Wt; a.bct = p.dev.bct; a.bct_coef = p.dev.bct_coef; a.kappa = p.dev.kappa;
+  a.Wf = (const T*)p.dev.Wf; a.bct = p.dev.bct; a.bct_coef = p.dev.bct_coef; a.kappa = p.dev.kappa;
   a.geo = make_geom(p);
   a.step = L.step;
   a.cdt = p.prob.c * p.prob.dt;

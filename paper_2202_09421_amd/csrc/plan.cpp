@@ -302,6 +302,23 @@ static void free_tables(DeviceTables& t) {
   t = DeviceTables();
 }
 
+// Wf[rt][k][h][lane][v]: what lane (node = lane % 16, r = lane / 16) of a wave
+// with row tile rt supplies to MFMA step 4 k + V h + v, V = values in 16 bytes.
+template <typename T>
+static std::vector<T> wf_order(const Plan& p, const std::vector<double>& Wt) {
+  constexpr int V = 16 / sizeof(T);
+  const int RT = (int)(p.Mpad / 16);
+  std::vector<T> out;
+  out.reserve(Wt.size());
+  for (int rt = 0; rt < RT; ++rt)
+    for (int k = 0; k < RT; ++k)
+      for (int h = 0; h < 4 / V; ++h)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int v = 0; v < V; ++v)
+            out.push_back((T)Wt[(size_t)(16 * k + 4 * (V * h + v) + lane / 16) * p.Mpad + 16 * rt + lane % 16]);
+  return out;
+}
+
 // Rows of a band of the state layout.  A node pass reads a node of every group
 // from up to eight arrays, a y line every row of one group.  With a whole
 // plane per group (one band) the node passes met the same memory channels
@@ -602,7 +619,8 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   TableUpload up;
   up.add(xi, &p.dev.xi);
   up.add(eta, &p.dev.eta);
-  up.add(Wt, &p.dev.Wt);
+  if (p.dtype == RTE_F64) up.add(wf_order<double>(p, Wt), reinterpret_cast<double**>(&p.dev.Wf));
+  else up.add(wf_order<float>(p, Wt), reinterpret_cast<float**>(&p.dev.Wf));
   up.add(bcc, &p.dev.bc);
   up.add(bcf, &p.dev.bc_coef);
   up.add(btc, &p.dev.bct);

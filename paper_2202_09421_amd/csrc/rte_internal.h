@@ -80,7 +80,9 @@ struct DeviceTables {
   // ordinates in storage order (slot s = 4*g + r)
   double* xi = nullptr;     // [M]
   double* eta = nullptr;    // [M]
-  double* Wt = nullptr;     // [Mpad16][Mpad16] HG matrix in slot order (zero padded)
+  // HG matrix in slot order, zero padded to 16, in the plan's type and the order
+  // of the MFMA operand: [row tile][column tile][piece][lane][16 bytes]
+  void* Wf = nullptr;
   // boundary rules [9][M]: packed flags and slots within the group, and the two
   // coefficients.  Forward: bit 0 flag, bits 1-2 src_a, 3-4 src_b.  Transpose:
   // bit 0 is_target, bits 1-2 ntgt, 3-4 tgt[0], 5-6 tgt[1]
