@@ -89,36 +89,51 @@ static bool smooth5(int64_t n) {
 }
 
 // ---------------------------------------------------------------- device upload helper
-// All tables of a plan in one device allocation, filled by one copy (an
-// allocation and a copy per table took most of the time of rte_plan_create on
-// small grids).  Tables start at multiples of 256 bytes.
+// All tables of a plan in one device allocation.  Those below 64 KiB go with
+// one copy (an allocation and a copy each took most of the time of
+// rte_plan_create on small grids: 90 us of 280 are left for 25 x 21 nodes), the
+// others from where they are (gathering the 10 MB of a 1025 x 1025 plan with
+// 128 detectors added 3.5 ms to its 6).  Tables start at multiples of 256
+// bytes; a vector given to add() has to live until commit().
 class TableUpload {
  public:
   template <typename V>
   void add(const std::vector<V>& h, V** d) {
     *d = nullptr;
-    if (h.empty()) return;
-    const size_t off = (host_.size() + 255) & ~size_t(255), n = h.size() * sizeof(V);
-    host_.resize(off + n);
-    std::memcpy(host_.data() + off, h.data(), n);
-    slots_.push_back({reinterpret_cast<void**>(d), off});
+    if (!h.empty()) slots_.push_back({reinterpret_cast<void**>(d), h.data(), h.size() * sizeof(V)});
   }
   bool commit(void** base) {
-    if (hipMalloc(base, host_.size()) != hipSuccess) {
+    size_t packed = 0, total = 0;
+    for (const Slot& s : slots_)
+      if (s.bytes < kOwnCopy) packed += pad(s.bytes);
+    total = packed;
+    for (const Slot& s : slots_)
+      if (s.bytes >= kOwnCopy) total += pad(s.bytes);
+    if (hipMalloc(base, total) != hipSuccess) {
       *base = nullptr;
       return false;
     }
-    if (hipMemcpy(*base, host_.data(), host_.size(), hipMemcpyHostToDevice) != hipSuccess) return false;
-    for (const Slot& s : slots_) *s.ptr = static_cast<char*>(*base) + s.off;
-    return true;
+    char* dev = static_cast<char*>(*base);
+    std::vector<char> host(packed);
+    size_t small = 0, large = packed;
+    for (const Slot& s : slots_) {
+      size_t& off = s.bytes < kOwnCopy ? small : large;
+      *s.ptr = dev + off;
+      if (s.bytes < kOwnCopy) std::memcpy(host.data() + off, s.src, s.bytes);
+      else if (hipMemcpy(dev + off, s.src, s.bytes, hipMemcpyHostToDevice) != hipSuccess) return false;
+      off += pad(s.bytes);
+    }
+    return packed == 0 || hipMemcpy(dev, host.data(), packed, hipMemcpyHostToDevice) == hipSuccess;
   }
 
  private:
+  static constexpr size_t kOwnCopy = 64 * 1024;
+  static size_t pad(size_t b) { return (b + 255) & ~size_t(255); }
   struct Slot {
     void** ptr;
-    size_t off;
+    const void* src;
+    size_t bytes;
   };
-  std::vector<char> host_;
   std::vector<Slot> slots_;
 };
 
@@ -619,8 +634,10 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   TableUpload up;
   up.add(xi, &p.dev.xi);
   up.add(eta, &p.dev.eta);
-  if (p.dtype == RTE_F64) up.add(wf_order<double>(p, Wt), reinterpret_cast<double**>(&p.dev.Wf));
-  else up.add(wf_order<float>(p, Wt), reinterpret_cast<float**>(&p.dev.Wf));
+  const std::vector<double> wf64 = p.dtype == RTE_F64 ? wf_order<double>(p, Wt) : std::vector<double>();
+  const std::vector<float> wf32 = p.dtype == RTE_F64 ? std::vector<float>() : wf_order<float>(p, Wt);
+  if (p.dtype == RTE_F64) up.add(wf64, reinterpret_cast<double**>(&p.dev.Wf));
+  else up.add(wf32, reinterpret_cast<float**>(&p.dev.Wf));
   up.add(bcc, &p.dev.bc);
   up.add(bcf, &p.dev.bc_coef);
   up.add(btc, &p.dev.bct);
@@ -635,7 +652,8 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   up.add(fcbuf, &p.dev.fc_buf);
   up.add(detsp, &p.dev.det_sp);
   up.add(srev, &p.dev.slot_rev);
-  up.add(std::vector<unsigned long long>(1, 0ull), &p.dev.guard_flag);
+  const std::vector<unsigned long long> guard(1, 0ull);
+  up.add(guard, &p.dev.guard_flag);
   if (!up.commit(&p.dev.base)) {
     set_error("device allocation or upload of the plan tables failed");
     free_tables(p.dev);
