@@ -66,7 +66,7 @@ struct Lines4Args {
   int G, d;
   int first, units_first;  // direction of units [0, units_first) of a (source, group)
   int nunits;              // units per (source, group)
-  int nt_out;              // non-temporal stores
+  int nt_out;              // non-temporal stores: bit 0 rows, bit 1 columns
 };
 
 constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v / 2); }
@@ -581,7 +581,7 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
   const uint32_t lout = (it ? ls : 0u) + 16u * pc;
   char* out = reinterpret_cast<char*>(a.out[dirn] + base);
   const double* src = bufd + 2 * (pc * SL * G::LSZ) + it;
-  if (a.nt_out) store_unit<G, T, true>(out, src, lout, pt, i0, n);
+  if (a.nt_out & (D.along_x ? 1 : 2)) store_unit<G, T, true>(out, src, lout, pt, i0, n);
   else store_unit<G, T, false>(out, src, lout, pt, i0, n);
 }
 

@@ -161,7 +161,13 @@ static hipError_t launch4_t(const Plan& p, const LineLaunch& L, hipStream_t s) {
   a.grp_stride = p.grp_stride;
   a.inst_stride = p.inst_stride;
   a.G = (int)p.G;
-  a.nt_out = p.line_nt ? 1 : 0;
+  // FP32 columns leave in 32-byte pieces per point, which a large plan's passes
+  // rather let the L2 merge with the neighbouring pair's: at more than 64 MiB a
+  // source, plain stores give 640 x 640 x 64 160 us a pass against 175,
+  // 1025 x 1025 x 64 448 against 493; below (385 x 385 x 64, four sources 234
+  // against 221) and in FP64 (700 x 700 x 64 240 against 207) the hint is better
+  const bool merge_y = p.dtype == RTE_F32 && p.inst_stride * (int64_t)sizeof(float) > kStreamNtBytes;
+  a.nt_out = p.line_nt ? (merge_y ? 1 : 3) : 0;
   a.first = dx ? 0 : 1;
   a.units_first = a.dir[a.first].npe;
   a.nunits = a.units_first + ((dx && dy) ? a.dir[1].npe : 0);
