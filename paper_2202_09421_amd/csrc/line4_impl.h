@@ -49,7 +49,8 @@ struct Lines4Dir {
   const double* mu;        // multipliers in the order of the last stage (line4_orders)
   const double* Mx;        // (C + E) x 2d continuation matrix [MR | ML]
   const double* MxT;       // its transpose [side][kMaxFcD][C + E], zero rows beyond d
-  int n, CE;               // nodes per line, extension points
+  const double2* tw;       // twiddle powers in job order (line4_orders)
+  int n, CE, Np;           // nodes per line, extension points, their sum
   int pr[kMaxFcD], pl[kMaxFcD];  // LDS positions of the matching values n - d + k and d - 1 - k (k < d; else 0)
   int nlines, npe;         // lines, line pairs rounded up to even
   bool along_x;            // lines are rows (else columns)
@@ -60,7 +61,6 @@ struct Lines4Args {
   const T* in;
   T* out[2];
   Lines4Dir dir[2];
-  const double2* tw;       // twiddle powers in job order (line4_orders)
   RowMap rows;
   int64_t grp_stride, inst_stride;
   int G, d;
@@ -444,22 +444,14 @@ __device__ __forceinline__ void store_unit(char* out, const double* src, uint32_
   }
 }
 
+// Lines line0 and line0 + 1 of direction D of the block's (source, group), by
+// the first G::NTH threads
 template <typename T, bool ADJ, int N1, int M>
-__global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T> a) {
+__device__ __forceinline__ void lines4_unit(const Lines4Args<T>& a, const Lines4Dir& D, T* dout, int line0, unsigned char* smem_raw) {
   typedef Geo<N1, M> G;
   constexpr int N = G::N, NTH = G::NTH, LPW = G::LPW;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<double>* buf = reinterpret_cast<cx<double>*>(smem_raw);
   double* bufd = reinterpret_cast<double*>(smem_raw);
-
-  // unit: direction and line pair of the block's (source, group)
-  const int u = remap_unit16((int)blockIdx.x);
-  if (u >= a.nunits) return;
-  const bool second = u >= a.units_first;
-  const int dirn = second ? 1 - a.first : a.first;
-  const Lines4Dir& D = a.dir[dirn];
-  const int line0 = 2 * (second ? u - a.units_first : u);
-  if (line0 >= D.nlines) return;
   const bool has1 = line0 + 1 < D.nlines;
   const int g = (int)blockIdx.y, s0 = g * kGroup;
   const int64_t l0 = D.along_x ? a.rows(line0) : line0 * kGroup;
@@ -484,7 +476,7 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
   // the lane's row of the continuation matrix (first job of the extension)
   MxRow row;
   if constexpr (!ADJ) row.load(D, dd, lane / LPW);
-  const double2* __restrict__ tw = a.tw;
+  const double2* __restrict__ tw = D.tw;
 #pragma unroll
   for (int c0 = 0; c0 < TMAX; c0 += CH) {
     V16 v[CH];
@@ -579,22 +571,40 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
 
   if (it && !has1) return;
   const uint32_t lout = (it ? ls : 0u) + 16u * pc;
-  char* out = reinterpret_cast<char*>(a.out[dirn] + base);
+  char* out = reinterpret_cast<char*>(dout + base);
   const double* src = bufd + 2 * (pc * SL * G::LSZ) + it;
   if (a.nt_out & (D.along_x ? 1 : 2)) store_unit<G, T, true>(out, src, lout, pt, i0, n);
   else store_unit<G, T, false>(out, src, lout, pt, i0, n);
 }
 
+template <typename T, bool ADJ, int N1, int M>
+__global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int u = remap_unit16((int)blockIdx.x);
+  if (u >= a.nunits) return;
+  const bool second = u >= a.units_first;
+  const int dirn = second ? 1 - a.first : a.first;
+  const int line0 = 2 * (second ? u - a.units_first : u);
+  if (line0 >= a.dir[dirn].nlines) return;
+  lines4_unit<T, ADJ, N1, M>(a, a.dir[dirn], a.out[dirn], line0, smem_raw);
+}
+
 constexpr size_t kLines4MaxLds = 160 * 1024;
+
+// LDS positions of the matching values
+template <int N1, int M>
+inline void set_positions(Lines4Dir& D, int d) {
+  typedef Geo<N1, M> G;
+  for (int k = 0; k < kMaxFcD; ++k) {
+    D.pr[k] = k < d ? G::pos(D.n - d + k) : 0;
+    D.pl[k] = k < d ? G::pos(d - 1 - k) : 0;
+  }
+}
 
 template <typename T, bool ADJ, int N1, int M>
 inline hipError_t go_one(Lines4Args<T> a, int nq, hipStream_t s) {
   typedef Geo<N1, M> G;
-  for (Lines4Dir& D : a.dir)
-    for (int k = 0; k < kMaxFcD; ++k) {
-      D.pr[k] = k < a.d ? G::pos(D.n - a.d + k) : 0;
-      D.pl[k] = k < a.d ? G::pos(a.d - 1 - k) : 0;
-    }
+  for (Lines4Dir& D : a.dir) set_positions<N1, M>(D, a.d);
   static_assert(G::bytes <= kLines4MaxLds, "line buffer exceeds the LDS of a CU");
   if (a.nunits == 0) return hipSuccess;
   const unsigned gx = (unsigned)(((a.nunits + 15) / 16) * 16);
@@ -602,6 +612,10 @@ inline hipError_t go_one(Lines4Args<T> a, int nq, hipStream_t s) {
   return hipGetLastError();
 }
 
+// both directions of unequal lengths in one launch; hipErrorNotSupported where
+// that is not built or not faster
+hipError_t lines4_mixed(const Lines4Args<double>& a, int nq, bool adj, hipStream_t s);
+hipError_t lines4_mixed(const Lines4Args<float>& a, int nq, bool adj, hipStream_t s);
 hipError_t lines4_extra0(const Lines4Args<double>& a, int Np, int nq, bool adj, hipStream_t s);
 hipError_t lines4_extra0(const Lines4Args<float>& a, int Np, int nq, bool adj, hipStream_t s);
 hipError_t lines4_extra1(const Lines4Args<double>& a, int Np, int nq, bool adj, hipStream_t s);

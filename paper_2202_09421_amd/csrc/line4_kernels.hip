@@ -146,6 +146,8 @@ static hipError_t launch4_t(const Plan& p, const LineLaunch& L, hipStream_t s) {
     D.mu = fc.mup;
     D.Mx = fc.Mx;
     D.MxT = fc.MxT;
+    D.tw = reinterpret_cast<const double2*>(fc.tw4);
+    D.Np = fc.Np;
     D.n = fc.n;
     D.CE = fc.C + fc.E;
     D.nlines = (int)(k ? p.nx : p.ny);
@@ -155,7 +157,6 @@ static hipError_t launch4_t(const Plan& p, const LineLaunch& L, hipStream_t s) {
   }
   const bool dx = (L.dirs & 1) != 0, dy = (L.dirs & 2) != 0;
   const FcPlanDev& fc = dx ? p.fcx : p.fcy;
-  a.tw = reinterpret_cast<const double2*>(fc.tw4);
   a.d = fc.d;
   a.rows = p.rows;
   a.grp_stride = p.grp_stride;
@@ -171,6 +172,7 @@ static hipError_t launch4_t(const Plan& p, const LineLaunch& L, hipStream_t s) {
   a.first = dx ? 0 : 1;
   a.units_first = a.dir[a.first].npe;
   a.nunits = a.units_first + ((dx && dy) ? a.dir[1].npe : 0);
+  if (dx && dy && p.fcx.Np != p.fcy.Np) return lines4_mixed(a, (int)p.cnq, L.mode == LINE_ADJ, s);
   return L.mode == LINE_ADJ ? by_size<T, true>(a, fc.Np, (int)p.cnq, s) : by_size<T, false>(a, fc.Np, (int)p.cnq, s);
 }
 

@@ -249,11 +249,12 @@ hipError_t launch_line_generic(const Plan& p, const void* in, void* out, int mod
   return mode == LINE_ADJ ? launch_mode<float, true>(p, in, out, dir, s) : launch_mode<float, false>(p, in, out, dir, s);
 }
 
-// Both line sets: one four-step launch when the extended lengths coincide,
-// otherwise one launch per direction (four-step where N_p has a split).
+// Both line sets: one four-step launch when the extended lengths coincide or
+// the grid is small, otherwise one launch per direction (four-step where N_p
+// has a split).
 hipError_t launch_lines(const Plan& p, const LineLaunch& L, hipStream_t s) {
   const bool four_x = p.fcx.n1 > 0 && !p.sched.line_generic, four_y = p.fcy.n1 > 0 && !p.sched.line_generic;
-  if (L.dirs == 3 && p.fcx.Np == p.fcy.Np && four_x && four_y) {
+  if (L.dirs == 3 && four_x && four_y) {
     const hipError_t e = launch_lines4(p, L, s);
     if (e != hipErrorNotSupported) return e;
   }
