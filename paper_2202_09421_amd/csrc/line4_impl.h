@@ -29,13 +29,15 @@
 // so a unit has two workgroup barriers in all.
 //
 // What bounds it (513 x 513 x 64, N = 540).  FP64, four sources: the streams,
-// 2.2 GB a launch at 4.8 TB/s (435 / 454 us forward / transpose; 594 / 603 us
+// 2.2 GB a launch at 4.7 TB/s (462 / 465 us forward / transpose; 594 / 603 us
 // with a barrier after each stage, two ordinates' values exchanged between
 // lanes to form complex entries, twiddles at every step and each stage's 80
-// to 108 jobs on a two-wave workgroup).  FP32: vector and LDS issue, each busy
-// for 57 % of the cycles (350 / 372 us; 540 / 571 us before).  At 257 x 257 x
-// 32 a CU has eight units, one round: 20.1 / 22.8 us in FP64 (24.6 / 25.9 us
-// before), 12 us of it the transforms.
+// to 108 jobs on a two-wave workgroup); with whole planes per group in memory
+// it ran at 5.0 TB/s, the columns of a banded state cost that (rows 213 us,
+// columns 247 us on 513 x 440).  FP32: vector and LDS issue, each busy for 57 %
+// of the cycles (364 / 375 us; 540 / 571 us before).  At 257 x 257 x 32 a CU
+// has eight units, one round: 18.9 / 20.7 us in FP64 (24.6 / 25.9 us before),
+// 12 us of it the transforms.
 
 #include "fft_codelets.h"
 #include "rte_internal.h"
