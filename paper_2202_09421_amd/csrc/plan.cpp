@@ -425,6 +425,13 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   p.chunk = (prob->combo_chunk > 0) ? std::min<int64_t>(prob->combo_chunk, p.Nq) : p.Nq;
   p.cq0 = 0;
   p.cnq = p.chunk;
+  // a forward that fits the static scratch of rte_forward_noalloc without the
+  // bands' padded rows has to fit it with them, or has none
+  if (workspace_bytes(p, false) > kNoallocBytes) {
+    const int64_t band = p.rows.band;
+    set_bands(p, p.ny);
+    if (workspace_bytes(p, false) > kNoallocBytes) set_bands(p, band);
+  }
   p.stream_nt = p.chunk * p.inst_stride * es > kStreamNtBytes;
   p.line_nt = p.chunk * p.inst_stride * es > kLineNtBytes;
   const int M = (int)p.M;

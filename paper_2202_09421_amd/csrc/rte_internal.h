@@ -203,6 +203,7 @@ int64_t state_elems(const Plan& p);
 // bytes between consecutive state arrays of the workspace
 int64_t state_stride_bytes(const Plan& p);
 int64_t workspace_bytes(const Plan& p, bool with_adjoint);
+constexpr int64_t kNoallocBytes = int64_t(128) << 20;  // static scratch of rte_forward_noalloc
 bool map_workspace(const Plan& p, void* base, int64_t bytes, bool with_adjoint, Workspace* ws);
 
 // ---------------------------------------------------------------- kernel launchers

@@ -32,3 +32,23 @@ def test_generic_lines_over_bands(ny):
         out[generic] = u.clone()
     assert rel(out[0].cpu(), out[1].cpu()) < 2e-10   # each within 1e-10 of the oracle
     plan.close()
+
+
+def test_padded_rows_do_not_cross_the_static_scratch():
+    """379 rows of 392 nodes: 127 MiB of forward workspace as they are, 131 MiB with 390 rows."""
+    import ctypes
+    from paper_2202_09421_amd import rte
+    spec = W.small_problem(N=391, M=16, K=3, Ny=378, seed=2, n_in=1.4, g=0.8, n_det=8)
+    plan = rte.Plan(spec, torch.float64)
+    lib = rte.lib()
+    lib.rte_forward_noalloc.argtypes = [ctypes.c_void_p] * 6
+    lib.rte_forward_noalloc.restype = ctypes.c_int
+    a, b = (torch.tensor(x, device="cuda") for x in (spec.mu_a, spec.mu_s))
+    G, u = plan.forward(a, b, want_u_final=True)
+    G2, u2 = torch.empty_like(G), torch.empty_like(u)
+    rc = lib.rte_forward_noalloc(plan._h, a.data_ptr(), b.data_ptr(), G2.data_ptr(), u2.data_ptr(),
+                                 torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, lib.rte_last_error().decode()
+    torch.cuda.synchronize()
+    assert torch.equal(G, G2) and torch.equal(u, u2)
+    plan.close()
