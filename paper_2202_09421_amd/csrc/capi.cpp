@@ -185,6 +185,22 @@ void mark_saved(Plan& p, const void* wsp, bool last_segment) {
   p.saved_ws = wsp;
 }
 
+// Called by every entry point that writes the segment store, before any work.
+// A call recorded by the caller's stream capture writes it whenever the
+// caller's graph is launched, or never, and the host does not see that.  From
+// the first recorded call on, last_segment says nothing about the device, and
+// adjoints of the plan replay the last segment like every other.
+void note_recording(Plan& p, hipStream_t st) {
+  if (p.recorded || p.K <= p.ckpt_every || p.ckpt_every == 0) return;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    p.recorded = true;
+  } else {
+    p.recorded = status != hipStreamCaptureStatusNone;
+  }
+}
+
 // Maps the workspace; RTE_EINVAL for a base that is not 256-byte aligned
 // (the kernels issue 16-byte vector accesses at offsets that are multiples
 // of 256 from it), RTE_ENOMEM for a buffer that is too small.
@@ -330,7 +346,7 @@ int run_adjoint(Plan& p, const void* mu_a, const void* mu_s, const double* Gbar,
   RTE_CHECK(launch_zero(ws.ga, gbytes, st));
   RTE_CHECK(launch_zero(ws.gb, gbytes, st));
   const int64_t nc = n_chunks(p);
-  const bool resident = p.last_segment;
+  const bool resident = p.last_segment && !p.recorded;
   p.last_segment = false;
   for (int64_t i = 0; i < nc; ++i) {
     const int64_t k = (p.saved_chunk + nc - i) % nc;  // saved chunk first
@@ -913,6 +929,7 @@ int rte_forward(rte_plan* h, const void* mu_a, const void* mu_s, double* G, void
     set_error("");
     Plan& p = *reinterpret_cast<Plan*>(h);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (save_states) note_recording(p, st);
     const int rc = run_forward(p, mu_a, mu_s, G, u_final, save_states, workspace, workspace_bytes, st);
     return rc != RTE_OK ? rc : guard_check(p, st, {{G, p.Nq * p.Nd * p.K}});
   } catch (const std::exception& e) {
@@ -930,6 +947,7 @@ int rte_adjoint(rte_plan* h, const void* mu_a, const void* mu_s, const double* G
     set_error("");
     Plan& p = *reinterpret_cast<Plan*>(h);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    note_recording(p, st);
     const int rc = run_adjoint(p, mu_a, mu_s, G_bar, dmu_a, dmu_s, workspace, workspace_bytes, st);
     return rc != RTE_OK ? rc : guard_check(p, st, {{dmu_a, p.nx * p.ny}, {dmu_s, p.nx * p.ny}});
   } catch (const std::exception& e) {
@@ -949,6 +967,7 @@ int rte_gradient(rte_plan* h, const void* mu_a, const void* mu_s, const double* 
     Plan& p = *reinterpret_cast<Plan*>(h);
     GradArgs a{mu_a, mu_s, G_meas, J, dmu_a, dmu_s, G, workspace, workspace_bytes};
     hipStream_t st = static_cast<hipStream_t>(stream);
+    note_recording(p, st);
     const int rc = p.use_graph ? graph_gradient(p, a, st) : enqueue_gradient(p, a, st);
     return rc != RTE_OK ? rc : guard_check(p, st, grad_outputs(p, a));
   } catch (const std::exception& e) {
@@ -999,6 +1018,7 @@ int rte_gradient_range(rte_plan* h, const void* mu_a, const void* mu_s, const do
     GradArgs a{mu_a, mu_s, G_meas, J, dmu_a, dmu_s, G, workspace, workspace_bytes};
     hipStream_t st = static_cast<hipStream_t>(stream);
     p.range_next = -1;
+    note_recording(p, st);
     int rc = enqueue_gradient_ops(p, a, st, first, last, nullptr);
     if (rc != RTE_OK) return rc;
     p.range_next = last < total ? last : -1;
@@ -1063,6 +1083,7 @@ int rte_gradient_continuous(rte_plan* h, const void* mu_a, const void* mu_s, con
     Plan& p = *reinterpret_cast<Plan*>(h);
     GradArgs a{mu_a, mu_s, G_meas, J, dmu_a, dmu_s, G, workspace, workspace_bytes};
     hipStream_t st = static_cast<hipStream_t>(stream);
+    note_recording(p, st);
     const int rc = enqueue_gradient_continuous(p, a, st);
     return rc != RTE_OK ? rc : guard_check(p, st, grad_outputs(p, a));
   } catch (const std::exception& e) {
@@ -1198,6 +1219,7 @@ int rte_batch_gradient(rte_batch* h, const void* const* mu_a, const void* const*
       key.insert(key.end(), k, k + 10);
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
+    for (Plan* p : b.plans) note_recording(*p, st);
     if (!b.gexec || key != b.key) {
       if (b.gexec) {
         RTE_CHECK(hipGraphExecDestroy(b.gexec));
