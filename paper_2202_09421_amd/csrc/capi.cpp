@@ -185,13 +185,14 @@ void mark_saved(Plan& p, const void* wsp, bool last_segment) {
   p.saved_ws = wsp;
 }
 
-// Called by every entry point that writes the segment store, before any work.
-// A call recorded by the caller's stream capture writes it whenever the
+// Called by every entry point that writes the stored states, before any work.
+// A call recorded by the caller's stream capture writes them whenever the
 // caller's graph is launched, or never, and the host does not see that.  From
-// the first recorded call on, last_segment says nothing about the device, and
-// adjoints of the plan replay the last segment like every other.
+// the first recorded call on, last_segment and saved_chunk say nothing about
+// the device: adjoints of the plan replay the last segment like every other,
+// and with several chunks recompute every chunk's forward.
 void note_recording(Plan& p, hipStream_t st) {
-  if (p.recorded || p.K <= p.ckpt_every || p.ckpt_every == 0) return;
+  if (p.recorded || (n_chunks(p) == 1 && (p.ckpt_every == 0 || p.K <= p.ckpt_every))) return;
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &status) != hipSuccess) {
     (void)hipGetLastError();
@@ -327,7 +328,8 @@ int run_forward(Plan& p, const void* mu_a, const void* mu_s, double* G, void* u_
 }
 
 // Adjoint of the last saved forward.  The chunk whose states are in the
-// workspace goes first; every other chunk's forward is recomputed.
+// workspace goes first; every other chunk's forward is recomputed (all of
+// them if calls of the plan were recorded, see note_recording).
 int run_adjoint(Plan& p, const void* mu_a, const void* mu_s, const double* Gbar, double* da, double* db, void* wsp,
                 int64_t wsb, hipStream_t st) {
   if (!p.have_forward) {
@@ -351,9 +353,10 @@ int run_adjoint(Plan& p, const void* mu_a, const void* mu_s, const double* Gbar,
   for (int64_t i = 0; i < nc; ++i) {
     const int64_t k = (p.saved_chunk + nc - i) % nc;  // saved chunk first
     set_chunk(p, k);
-    int rc = (i == 0) ? RTE_OK : forward_chunk(c, true, nullptr);
+    const bool stored = i == 0 && !(p.recorded && nc > 1);
+    int rc = stored ? RTE_OK : forward_chunk(c, true, nullptr);
     if (rc == RTE_OK && launch_inject(p, Gbar, ws.flux, (int)p.K, st) != hipSuccess) rc = RTE_EDEVICE;
-    if (rc == RTE_OK) rc = adjoint_chunk(c, i > 0 || resident);
+    if (rc == RTE_OK) rc = adjoint_chunk(c, !stored || resident);
     if (rc != RTE_OK) {
       reset_chunk(p);
       if (rc == RTE_EDEVICE && last_error()[0] == '\0') set_error("injection kernel launch failed");

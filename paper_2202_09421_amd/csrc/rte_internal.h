@@ -147,7 +147,7 @@ struct Plan {
   int64_t saved_chunk = -1;    // chunk whose forward states are in the workspace
   bool have_forward = false;   // a saved forward lives in the workspace
   bool last_segment = false;   // its last checkpoint segment's states are still in the segment store
-  bool recorded = false;       // a call was recorded into a caller's graph: last_segment is not to be relied on
+  bool recorded = false;       // a call was recorded into a caller's graph: these two are not to be relied on
   int64_t saved_K = 0;
   const void* saved_ws = nullptr;  // workspace base of the saved forward
   // staged gradient (rte_gradient_range): next op expected and the

@@ -1,10 +1,10 @@
 """GPU: a recorded rte_adjoint of a checkpointed forward.
 
 A recording is launched with other cotangents, after other calls on the same
-workspace, and before eager adjoints of the same forward.  The segment store
-then holds the states that the last of these calls left there, which the host
-cannot know; every result must still have the bits of a plan that keeps every
-state and is called eagerly."""
+workspace, and before eager adjoints of the same forward.  The stored states
+are then those of the segment, or of the chunk of sources, that the last of
+these calls left there, which the host cannot know; every result must still
+have the bits of a plan that keeps every state and is called eagerly."""
 import numpy as np
 import pytest
 import torch
@@ -30,8 +30,8 @@ def _record(call):
     return g, out
 
 
-@pytest.mark.parametrize("ckpt", [1, 2, 3, 5, K - 1, K])
-def test_recorded_adjoint_is_idempotent(ckpt):
+@pytest.mark.parametrize("ckpt,chunk", [(1, 0), (2, 0), (3, 0), (5, 0), (K - 1, 0), (K, 0), (0, 1), (3, 1), (K, 1)])
+def test_recorded_adjoint_is_idempotent(ckpt, chunk):
     from paper_2202_09421_amd import rte
     spec = _spec()
     a, b = (torch.tensor(x, device="cuda") for x in (spec.mu_a, spec.mu_s))
@@ -42,7 +42,7 @@ def test_recorded_adjoint_is_idempotent(ckpt):
     ref_plan.forward(a, b, save_states=True)
     ref = [[x.clone() for x in ref_plan.adjoint(g, a, b)] for g in cot]
 
-    plan = rte.Plan(spec, torch.float64, ckpt_every=ckpt)
+    plan = rte.Plan(spec, torch.float64, ckpt_every=ckpt, combo_chunk=chunk)
     bar = torch.empty_like(cot[0])
     gm = torch.zeros_like(bar)
     plan.gradient(a, b, gm)
@@ -53,7 +53,7 @@ def test_recorded_adjoint_is_idempotent(ckpt):
     def same(got, k, what):
         torch.cuda.synchronize()
         for x, y in zip(got, ref[k]):
-            assert torch.equal(x, y), (ckpt, what, k)
+            assert torch.equal(x, y), (ckpt, chunk, what, k)
 
     for k in (0, 1, 2):              # replays with other cotangents
         bar.copy_(cot[k])
