@@ -15,6 +15,8 @@ theta, sigma_x, sigma_theta, tau, sigma_t, t0, group) and a list
 from __future__ import annotations
 
 import ctypes
+import functools
+import hashlib
 import json
 import os
 
@@ -125,6 +127,21 @@ def lib():
             getattr(L, f).restype = ctypes.c_int
         _lib = L
     return _lib
+
+
+@functools.lru_cache(maxsize=4)
+def _file_digest(path, size, mtime_ns):
+    h = hashlib.blake2b(digest_size=8)
+    with open(path, "rb") as fh:
+        while block := fh.read(1 << 20):
+            h.update(block)
+    return h.hexdigest()
+
+
+def _lib_digest():
+    """Digest of the built library (read once while the file stays the same)."""
+    st = os.stat(LIB_PATH)
+    return _file_digest(LIB_PATH, st.st_size, st.st_mtime_ns)
 
 
 def _check(rc):
@@ -270,15 +287,21 @@ class Plan:
         _check(lib().rte_plan_set_schedule(self._h, ctypes.byref(sc)))
 
     def tune_key(self):
+        """Key of this plan's shapes in the autotuner's cache.  It names the
+        library's build: which kernels a schedule field selects, and how fast
+        they are, is a property of the build that timed them (a choice of the
+        generic line kernel from before its length had a split kernel costs
+        1000 x 1000 x 64 3930 us a pass against 440)."""
         sp = self.spec
         dev = torch.cuda.get_device_name(self.device) if torch.cuda.is_available() else "none"
-        return "%s|%s|nx%d|ny%d|M%d|Nq%d|Np%d,%d" % (dev, "f64" if self.dtype == torch.float64 else "f32",
-                                                     sp.Nx + 1, sp.Ny + 1, sp.M, self.Nq, self.Np_x, self.Np_y)
+        return "%s|%s|nx%d|ny%d|M%d|Nq%d|Np%d,%d|lib%s" % (dev, "f64" if self.dtype == torch.float64 else "f32",
+                                                           sp.Nx + 1, sp.Ny + 1, sp.M, self.Nq, self.Np_x, self.Np_y,
+                                                           _lib_digest())
 
     def autotune(self, mu_a, mu_s, cache=None):
         """Pick the fastest launch schedule for this plan's shapes with the
         library's autotuner (rte_plan_autotune) and apply it.  `cache`: a JSON
-        file of earlier choices keyed by device and shapes (default
+        file of earlier choices keyed by device, shapes and library build (default
         $RTE_TUNE_CACHE or ~/.cache/rte_fcdom/schedules.json; False disables);
         a hit applies the stored schedule without timing."""
         path = None
