@@ -419,10 +419,12 @@ struct MxRow {
   }
 };
 
-// byte offset of point i of a line
+// byte offset of point i of a line (columns: the terms of RowMap)
 struct PtMap {
-  uint32_t inv, ps, skip;
-  __device__ __forceinline__ uint32_t operator()(int i) const { return (uint32_t)i * ps + __umulhi((uint32_t)i, inv) * skip; }
+  uint32_t inv, ps, skip, most;
+  __device__ __forceinline__ uint32_t operator()(int i) const {
+    return (uint32_t)i * ps + min(__umulhi((uint32_t)i, inv) * skip, most);
+  }
 };
 
 // Stores of one lane: its piece of every PT-th point.  NT: non-temporal, for
@@ -456,7 +458,7 @@ __device__ __forceinline__ void lines4_unit(const Lines4Args<T>& a, const Lines4
   double* bufd = reinterpret_cast<double*>(smem_raw);
   const bool has1 = line0 + 1 < D.nlines;
   const int g = (int)blockIdx.y, s0 = g * kGroup;
-  const int64_t l0 = D.along_x ? a.rows(line0) : line0 * kGroup;
+  const uint32_t l0 = D.along_x ? a.rows(line0, g) : (uint32_t)line0 * kGroup;
   const int64_t base = (int64_t)blockIdx.z * a.inst_stride + (int64_t)g * a.grp_stride + l0;
   const int n = D.n, CE = D.CE, dd = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -470,9 +472,10 @@ __device__ __forceinline__ void lines4_unit(const Lines4Args<T>& a, const Lines4
 
   // byte offsets from the unit's base fit 32 bits (one source's state is below 4 GiB)
   const char* in = reinterpret_cast<const char*>(a.in + base);
-  const uint32_t ls = (uint32_t)(((D.along_x ? a.rows(line0 + 1) : (line0 + 1) * kGroup) - l0) * sizeof(T));
-  const PtMap pt{a.rows.inv, (uint32_t)((D.along_x ? kGroup : a.rows.row) * sizeof(T)),
-                 D.along_x ? 0u : (uint32_t)(a.rows.skip * sizeof(T))};
+  const uint32_t ls = ((D.along_x ? a.rows(line0 + 1, g) : (uint32_t)(line0 + 1) * kGroup) - l0) * (uint32_t)sizeof(T);
+  const PtMap pt{a.rows.inv, (D.along_x ? (uint32_t)kGroup : a.rows.row) * (uint32_t)sizeof(T),
+                 D.along_x ? 0u : a.rows.skip * (uint32_t)sizeof(T),
+                 (a.rows.most - (uint32_t)g * a.rows.cut) * (uint32_t)sizeof(T)};
   const uint32_t lin = ((it && has1) ? ls : 0u) + 16u * pc;
   constexpr int CH = TMAX < 20 ? TMAX : (TMAX + 1) / 2;
   // the lane's row of the continuation matrix (first job of the extension)

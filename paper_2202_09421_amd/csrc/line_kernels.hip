@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(LineArgs<T> a) {
   // reach |A| ~ 5e3, so in FP32 it would lose ~4 digits
   cplx<double>* cs = reinterpret_cast<cplx<double>*>(bufB + 2 * Np);
 
-  const int64_t base = (int64_t)q * a.inst_stride + (int64_t)g * a.grp_stride + (a.along_x ? a.rows(line) : line * kGroup);
+  const int64_t base = (int64_t)q * a.inst_stride + (int64_t)g * a.grp_stride + (a.along_x ? a.rows(line, g) : line * kGroup);
   const T* in = a.in + base;
   const int s0 = g * kGroup;
 
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(LineArgs<T> a) {
 
   // ---- load the line (4 slots per point) into two complex lines
   for (int i = tid; i < n; i += nthr) {
-    const T* p = in + (a.along_x ? i * kGroup : a.rows(i));
+    const T* p = in + (a.along_x ? i * kGroup : a.rows(i, g));
     const CT v0 = p[0], v1 = p[1], v2 = p[2], v3 = p[3];
     bufA[i] = {v0 * cf[0], v1 * cf[1]};
     bufA[Np + i] = {v2 * cf[2], v3 * cf[3]};
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(LineArgs<T> a) {
         dv[3] += gs[(1 * 2 + 0) * kMaxFcD + k].im;
       }
     }
-    const int64_t off = a.along_x ? i * kGroup : a.rows(i);
+    const int64_t off = a.along_x ? i * kGroup : a.rows(i, g);
 #pragma unroll
     for (int r = 0; r < 4; ++r) out[off + r] = T(c4[r] * dv[r]);
   }

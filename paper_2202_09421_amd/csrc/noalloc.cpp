@@ -11,7 +11,8 @@
 
 #include "rte_internal.h"
 
-static __device__ __align__(256) unsigned char scratch[rte::kNoallocBytes];
+static constexpr int64_t kScratchBytes = int64_t(128) << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 
@@ -54,16 +55,16 @@ extern "C" int rte_forward_noalloc(rte_plan* h, const void* mu_a, const void* mu
     rte::set_error("");
     rte::Plan& p = *reinterpret_cast<rte::Plan*>(h);
     const int64_t need = rte::workspace_bytes(p, false);
-    if (need > rte::kNoallocBytes) {
+    if (need > kScratchBytes) {
       std::ostringstream o;
       o << "rte_forward_noalloc: this forward needs " << need << " bytes of device scratch, the static scratch "
-        << "holds " << rte::kNoallocBytes << " (use rte_forward with a workspace)";
+        << "holds " << kScratchBytes << " (use rte_forward with a workspace)";
       rte::set_error(o.str());
       return RTE_ENOMEM;
     }
     void* ptr = nullptr;
     if (int rc = scratch_for_current_device(&ptr)) return rc;
-    return rte::forward_into(p, mu_a, mu_s, G, u_final, ptr, rte::kNoallocBytes, static_cast<hipStream_t>(stream));
+    return rte::forward_into(p, mu_a, mu_s, G, u_final, ptr, kScratchBytes, static_cast<hipStream_t>(stream));
   } catch (const std::exception& e) {
     rte::set_error(e.what());
     return RTE_EINVAL;

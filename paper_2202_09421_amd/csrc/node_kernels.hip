@@ -238,6 +238,10 @@ __device__ __forceinline__ void st4(T* base, const uint32_t* off, const bool* ok
       if (ok[v]) sto<NT>(base, off[v], x[v]);
   }
 }
+// elements between the groups of row j
+__device__ __forceinline__ uint32_t row_grp_stride(const NodeGeom& G, int j) {
+  return (uint32_t)G.grp_stride - (j >= G.rows.last ? G.rows.cut : 0u);
+}
 // Lane offsets and masks of the 4 values.
 template <typename T>
 __device__ __forceinline__ void lane_offsets(const NodeGeom& G, const TileLane& t, uint32_t* off, bool* ok) {
@@ -245,7 +249,7 @@ __device__ __forceinline__ void lane_offsets(const NodeGeom& G, const TileLane& 
   for (int v = 0; v < 4; ++v) {
     const int s = lane_slot<T>(t, v);
     ok[v] = t.valid && (s >> 2) < G.G;
-    off[v] = (uint32_t)(((uint32_t)(s >> 2) * (uint32_t)G.grp_stride + (uint32_t)G.rows(t.j) + (uint32_t)t.i * kGroup + (s & 3)) * sizeof(T));
+    off[v] = (uint32_t)(((uint32_t)(s >> 2) * row_grp_stride(G, t.j) + G.rows(t.j, 0) + (uint32_t)t.i * kGroup + (s & 3)) * sizeof(T));
   }
 }
 // Byte offset of the value at the reversed ordinate of the lane's value v
@@ -253,7 +257,7 @@ __device__ __forceinline__ void lane_offsets(const NodeGeom& G, const TileLane& 
 template <typename T>
 __device__ __forceinline__ uint32_t pair_offset(const NodeGeom& G, const TileLane& t, const int32_t* slot_rev, int v) {
   const int sr = slot_rev[lane_slot<T>(t, v)];
-  return (uint32_t)(((uint32_t)(sr >> 2) * (uint32_t)G.grp_stride + (uint32_t)G.rows(t.j) + (uint32_t)t.i * kGroup + (sr & 3)) * sizeof(T));
+  return (uint32_t)(((uint32_t)(sr >> 2) * row_grp_stride(G, t.j) + G.rows(t.j, 0) + (uint32_t)t.i * kGroup + (sr & 3)) * sizeof(T));
 }
 // Value of slot c (0..3) of the group that holds the lane's value v, for the
 // same node: another lane's register (FP64) or one of the lane's own (FP32).
@@ -985,7 +989,7 @@ __global__ void unpermute_kernel(const T* __restrict__ st, T* __restrict__ out, 
   const int q = (int)(t / (M * Nn));
   const int g = s / kGroup, r = s % kGroup;
   const int64_t j = gn / nx, i = gn - j * nx;
-  const T v = st[(int64_t)q * inst_stride + (int64_t)g * grp_stride + rows((int)j) + i * kGroup + r];
+  const T v = st[(int64_t)q * inst_stride + (int64_t)g * grp_stride + rows((int)j, g) + i * kGroup + r];
   out[((int64_t)q * Nn + gn) * M + slot_m[s]] = v;
 }
 
@@ -1000,7 +1004,7 @@ __global__ void permute_kernel(const T* __restrict__ in, T* __restrict__ st, con
   const int q = (int)(t / (M * Nn));
   const int g = s / kGroup, r = s % kGroup;
   const int64_t j = gn / nx, i = gn - j * nx;
-  st[(int64_t)q * inst_stride + (int64_t)g * grp_stride + rows((int)j) + i * kGroup + r] = in[((int64_t)q * Nn + gn) * M + slot_m[s]];
+  st[(int64_t)q * inst_stride + (int64_t)g * grp_stride + rows((int)j, g) + i * kGroup + r] = in[((int64_t)q * Nn + gn) * M + slot_m[s]];
 }
 
 // Scalar flux of a state, eq. (photondensity) with the trapezoid rule on the
@@ -1014,9 +1018,10 @@ __global__ void flux_map_kernel(const T* __restrict__ st, double* __restrict__ o
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= nx) return;
   const int j = (int)blockIdx.y, q = (int)blockIdx.z;
-  const T* p = st + (int64_t)q * inst_stride + rows(j) + (int64_t)i * kGroup;
+  const T* p = st + (int64_t)q * inst_stride + rows(j, 0) + (int64_t)i * kGroup;
+  const int64_t gs = grp_stride - (j >= rows.last ? rows.cut : 0);
   double acc = 0.0;
-  for (int s = 0; s < M; ++s) acc += (double)p[(int64_t)(s / kGroup) * grp_stride + s % kGroup];
+  for (int s = 0; s < M; ++s) acc += (double)p[(int64_t)(s / kGroup) * gs + s % kGroup];
   out[(int64_t)q * out_q_stride + (int64_t)j * nx + i] = dth * acc;
 }
 

@@ -334,35 +334,35 @@ static std::vector<T> wf_order(const Plan& p, const std::vector<double>& Wt) {
   return out;
 }
 
-// Rows of a band of the state layout.  A node pass reads a node of every group
-// from up to eight arrays, a y line every row of one group.  With a whole
-// plane per group (one band) the node passes met the same memory channels
-// again and again at some plane sizes; with one row per band they do not, but
-// the rows of a y line are then G pitches apart.  Bands of 11-21 rows serve
-// both, odd ones only: a power-of-two step between bands brings the clashes
-// back.  Both line and both node passes together, M = 64, us, planes / 1 row /
-// 16 rows / 15 rows: 513 x 513 x 4 sources FP64 2690 / 2717 / 2572 / 2536,
-// 1025 x 1025 FP32 2092 / 2179 / 2138 / 1889, 1025 x 1025 FP64 2672 / 2661 /
-// 2608 / 2560, 513 x 513 x 4 FP32 1657 / 1748 / 1651 / 1663; at 257 nodes and
-// below all are within 3 %.  15 rows, or the height of those measured good at
-// ten sizes that pads fewer, where 15 would pad more than a 32nd.
-static int64_t band_rows(int64_t ny) {
-  int64_t best = 0, pad = 0;
-  for (int64_t b : {15, 13, 17, 19, 11}) {
-    const int64_t q = (b - ny % b) % b;
-    if (best == 0 || (pad * 32 > ny && q < pad)) best = b, pad = q;
-  }
-  return std::min(best, ny);
-}
+// Rows of a band of the state layout (the last band holds what is left: padded
+// to a whole band, a state of 513 rows took 2.3 % more memory, one of 46 rows
+// 13 %).  A node pass reads a node of every group from up to eight arrays, a y
+// line every row of one group.  With a whole plane per group (one band) the
+// node passes met the same memory channels again and again at some plane sizes;
+// with one row per band they do not, but the rows of a y line are then G pitches
+// apart.  Bands of 11-21 rows serve both, odd ones only: a power-of-two step
+// between bands brings the clashes back.  Both line and both node passes
+// together, M = 64, us, planes / 1 row / 16 rows / 15 rows (last band padded):
+// 513 x 513 x 4 sources FP64 2690 / 2717 / 2572 / 2536, 1025 x 1025 FP32 2092 /
+// 2179 / 2138 / 1889, 1025 x 1025 FP64 2672 / 2661 / 2608 / 2560, 513 x 513 x 4
+// FP32 1657 / 1748 / 1651 / 1663; at 257 nodes and below all are within 3 %.
+// 13 rows / 15 rows: 201 x 201 x 32 FP64 55.6 / 56.1, 301 x 190 x 20 x 2 113.6 /
+// 113.8, 321 x 321 x 32 123.9 / 124.5, 385 x 385 x 64 350.3 / 351.1, 449 x 449 x
+// 64 equal, 513 x 513 x 64 x 4 2475 / 2465.
+static int64_t band_rows(int64_t ny) { return std::min<int64_t>(ny < 400 ? 13 : 15, ny); }
 
-static void set_bands(Plan& p, int64_t band) {
-  p.rows.band = (int)band;
+static void set_bands(Plan& p) {
+  const int64_t band = band_rows(p.ny), last = (p.ny - 1) / band * band;
+  const int64_t row = p.nxp * kGroup, skip = (p.G - 1) * band * row;
+  p.grp_stride = band * row;
+  p.inst_stride = p.G * p.ny * row;
+  // (32 bits hold these where plan_create accepts inst_stride)
   p.rows.inv = (uint32_t)((int64_t(1) << 32) / band + 1);
-  p.rows.row = p.nxp * kGroup;
-  p.grp_stride = band * p.rows.row;
-  const int64_t band_stride = p.G * p.grp_stride;
-  p.rows.skip = band_stride - p.grp_stride;
-  p.inst_stride = (p.ny + band - 1) / band * band_stride;
+  p.rows.row = (uint32_t)row;
+  p.rows.skip = (uint32_t)skip;
+  p.rows.most = (uint32_t)(last / band * skip);
+  p.rows.cut = (uint32_t)((last + band - p.ny) * row);
+  p.rows.last = (int)last;
 }
 
 int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams, const rte_detector* dets,
@@ -405,10 +405,9 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
     const int64_t pitch = p.nxp * kGroup * (prob->dtype == RTE_F64 ? 8 : 4);
     if (pitch % 2048 == 0) p.nxp += align;
   }
-  const int64_t es = (prob->dtype == RTE_F64) ? 8 : 4, limit = (int64_t(1) << 32) / es;
-  set_bands(p, band_rows(p.ny));
-  if (p.inst_stride >= limit) set_bands(p, p.ny);  // no padded rows
-  if (p.inst_stride >= limit) {
+  const int64_t es = (prob->dtype == RTE_F64) ? 8 : 4;
+  set_bands(p);
+  if (p.inst_stride * es >= (int64_t(1) << 32)) {
     set_error("one source's state exceeds 4 GiB (ordinates x nodes too large)");
     delete P;
     return RTE_EUNSUPPORTED;
@@ -425,13 +424,6 @@ int plan_create(const rte_problem* prob, const rte_beam* beams, int64_t n_beams,
   p.chunk = (prob->combo_chunk > 0) ? std::min<int64_t>(prob->combo_chunk, p.Nq) : p.Nq;
   p.cq0 = 0;
   p.cnq = p.chunk;
-  // a forward that fits the static scratch of rte_forward_noalloc without the
-  // bands' padded rows has to fit it with them, or has none
-  if (workspace_bytes(p, false) > kNoallocBytes) {
-    const int64_t band = p.rows.band;
-    set_bands(p, p.ny);
-    if (workspace_bytes(p, false) > kNoallocBytes) set_bands(p, band);
-  }
   p.stream_nt = p.chunk * p.inst_stride * es > kStreamNtBytes;
   p.line_nt = p.chunk * p.inst_stride * es > kLineNtBytes;
   const int M = (int)p.M;
