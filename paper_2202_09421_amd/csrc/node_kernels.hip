@@ -854,48 +854,55 @@ hipError_t launch_node_adj(const Plan& p, const NodeAdjLaunch& L, hipStream_t s)
 // G[q][jd][k] = sum_{w,pos} det_w[jd][w][pos] flux[q][k+1][w][pos].  A block
 // forms kDetK time levels x kDetJ detectors; its lanes run along the boundary,
 // so rows and weights are read in whole lines and each is used kDetJ / kDetK
-// times.  Sums: per lane, the 64 lanes, the 4 waves, in a fixed order.  (One
+// times.  Sums: per lane, the 64 lanes, the 4 waves, in a fixed order.  Up to
+// kDetBlocks blocks a source, which then take further tiles in turn (a launch
+// holds 2^32 threads along x, 1.3e8 outputs at a tile a block).  (One
 // thread per output, reading a row of its own, took 198 us for 32 detectors,
 // 120 levels and 1028 boundary positions, as long as two time steps; this takes
 // 7 us.)
 constexpr int kDetK = 2, kDetJ = 4;
+constexpr int64_t kDetBlocks = int64_t(1) << 20;
 __global__ __launch_bounds__(256) void detect_kernel(const double* __restrict__ flux, const double* __restrict__ dw,
                                                      double* __restrict__ G, int q0, int Nd, int K, int npos) {
   __shared__ double red[4][kDetK * kDetJ];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const unsigned nj = (unsigned)(Nd + kDetJ - 1) / kDetJ;   // blocks x: detectors fastest
-  const int q = q0 + (int)blockIdx.y, k0 = (int)(blockIdx.x / nj) * kDetK, j0 = (int)(blockIdx.x % nj) * kDetJ;
-  const int X = 4 * npos;
-  // rows and detectors beyond the last repeat it and are not written
-  const double* f[kDetK];
-  const double* w[kDetJ];
+  const unsigned nj = (unsigned)(Nd + kDetJ - 1) / kDetJ;   // tiles of a source: detectors fastest
+  const int64_t ntiles = (int64_t)((K + kDetK - 1) / kDetK) * nj;
+  const int q = q0 + (int)blockIdx.y, X = 4 * npos;
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int k0 = (int)(tile / nj) * kDetK, j0 = (int)(tile % nj) * kDetJ;
+    // rows and detectors beyond the last repeat it and are not written
+    const double* f[kDetK];
+    const double* w[kDetJ];
 #pragma unroll
-  for (int k = 0; k < kDetK; ++k) f[k] = flux + ((int64_t)q * (K + 1) + min(k0 + k, K - 1) + 1) * X;
+    for (int k = 0; k < kDetK; ++k) f[k] = flux + ((int64_t)q * (K + 1) + min(k0 + k, K - 1) + 1) * X;
 #pragma unroll
-  for (int j = 0; j < kDetJ; ++j) w[j] = dw + (int64_t)min(j0 + j, Nd - 1) * X;
-  double acc[kDetK * kDetJ] = {};
+    for (int j = 0; j < kDetJ; ++j) w[j] = dw + (int64_t)min(j0 + j, Nd - 1) * X;
+    double acc[kDetK * kDetJ] = {};
 #pragma unroll 2
-  for (int x = tid; x < X; x += 256) {
-    double fv[kDetK];
+    for (int x = tid; x < X; x += 256) {
+      double fv[kDetK];
 #pragma unroll
-    for (int k = 0; k < kDetK; ++k) fv[k] = f[k][x];
+      for (int k = 0; k < kDetK; ++k) fv[k] = f[k][x];
 #pragma unroll
-    for (int j = 0; j < kDetJ; ++j) {
-      const double wv = w[j][x];
+      for (int j = 0; j < kDetJ; ++j) {
+        const double wv = w[j][x];
 #pragma unroll
-      for (int k = 0; k < kDetK; ++k) acc[k * kDetJ + j] += wv * fv[k];
+        for (int k = 0; k < kDetK; ++k) acc[k * kDetJ + j] += wv * fv[k];
+      }
     }
-  }
 #pragma unroll
-  for (int e = 0; e < kDetK * kDetJ; ++e) {
+    for (int e = 0; e < kDetK * kDetJ; ++e) {
 #pragma unroll
-    for (int m = 32; m > 0; m >>= 1) acc[e] += __shfl_xor(acc[e], m);
-    if (lane == 0) red[wave][e] = acc[e];
-  }
-  __syncthreads();
-  if (tid < kDetK * kDetJ) {
-    const int k = k0 + tid / kDetJ, j = j0 + tid % kDetJ;
-    if (k < K && j < Nd) G[((int64_t)q * Nd + j) * K + k] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+      for (int m = 32; m > 0; m >>= 1) acc[e] += __shfl_xor(acc[e], m);
+      if (lane == 0) red[wave][e] = acc[e];
+    }
+    __syncthreads();
+    if (tid < kDetK * kDetJ) {
+      const int k = k0 + tid / kDetJ, j = j0 + tid % kDetJ;
+      if (k < K && j < Nd) G[((int64_t)q * Nd + j) * K + k] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+    }
+    __syncthreads();   // red is read before the next tile writes it
   }
 }
 
@@ -1057,7 +1064,8 @@ hipError_t launch_zero(void* p, int64_t bytes, hipStream_t s) {
 // detect, inject and misfit work on the sources of the current chunk
 hipError_t launch_detect(const Plan& p, const double* flux, double* G, int K, hipStream_t s) {
   if (p.cnq * p.Nd * K == 0) return hipSuccess;
-  const dim3 grid((unsigned)((K + kDetK - 1) / kDetK * ((p.Nd + kDetJ - 1) / kDetJ)), (unsigned)p.cnq);
+  const int64_t tiles = (K + kDetK - 1) / kDetK * ((p.Nd + kDetJ - 1) / kDetJ);
+  const dim3 grid((unsigned)std::min(tiles, kDetBlocks), (unsigned)p.cnq);
   hipLaunchKernelGGL(detect_kernel, grid, dim3(256), 0, s, flux, p.dev.det_w, G, (int)p.cq0, (int)p.Nd, K, (int)p.npos);
   return hipGetLastError();
 }
