@@ -449,9 +449,12 @@ __device__ __forceinline__ void store_unit(char* out, const double* src, uint32_
 }
 
 // Lines line0 and line0 + 1 of direction D of the block's (source, group), by
-// the first G::NTH threads
+// the first G::NTH threads.  All waves of the block call this, those beyond with
+// active = false (the same for a whole wave): they share the barriers and do
+// nothing else.
 template <typename T, bool ADJ, int N1, int M>
-__device__ __forceinline__ void lines4_unit(const Lines4Args<T>& a, const Lines4Dir& D, T* dout, int line0, unsigned char* smem_raw) {
+__device__ __forceinline__ void lines4_unit(const Lines4Args<T>& a, const Lines4Dir& D, T* dout, int line0, unsigned char* smem_raw,
+                                            bool active) {
   typedef Geo<N1, M> G;
   constexpr int N = G::N, NTH = G::NTH, LPW = G::LPW;
   cx<double>* buf = reinterpret_cast<cx<double>*>(smem_raw);
@@ -480,101 +483,105 @@ __device__ __forceinline__ void lines4_unit(const Lines4Args<T>& a, const Lines4
   constexpr int CH = TMAX < 20 ? TMAX : (TMAX + 1) / 2;
   // the lane's row of the continuation matrix (first job of the extension)
   MxRow row;
-  if constexpr (!ADJ) row.load(D, dd, lane / LPW);
   const double2* __restrict__ tw = D.tw;
+  if (active) {
+    if constexpr (!ADJ) row.load(D, dd, lane / LPW);
 #pragma unroll
-  for (int c0 = 0; c0 < TMAX; c0 += CH) {
-    V16 v[CH];
+    for (int c0 = 0; c0 < TMAX; c0 += CH) {
+      V16 v[CH];
 #pragma unroll
-    for (int t = 0; t < CH; ++t) {
-      const int i = i0 + PT * (c0 + t);
-      if (c0 + t < TMAX) v[t] = *reinterpret_cast<const V16*>(in + (lin + pt(min(i, n - 1))));
-    }
-    if (!has1 && it) {
+      for (int t = 0; t < CH; ++t) {
+        const int i = i0 + PT * (c0 + t);
+        if (c0 + t < TMAX) v[t] = *reinterpret_cast<const V16*>(in + (lin + pt(min(i, n - 1))));
+      }
+      if (!has1 && it) {
 #pragma unroll
-      for (int t = 0; t < CH; ++t) v[t] = V16(T(0));
-    }
+        for (int t = 0; t < CH; ++t) v[t] = V16(T(0));
+      }
 #pragma unroll
-    for (int t = 0; t < CH; ++t) {
-      const int i = i0 + PT * (c0 + t);
-      if (c0 + t < TMAX && i < n) {
-        double* q = bufd + 2 * (G::pos(i) + pc * SL * G::LSZ) + it;
+      for (int t = 0; t < CH; ++t) {
+        const int i = i0 + PT * (c0 + t);
+        if (c0 + t < TMAX && i < n) {
+          double* q = bufd + 2 * (G::pos(i) + pc * SL * G::LSZ) + it;
 #pragma unroll
-        for (int r = 0; r < SL; ++r) q[2 * r * G::LSZ] = (double)v[t][r];
+          for (int r = 0; r < SL; ++r) q[2 * r * G::LSZ] = (double)v[t][r];
+        }
       }
     }
   }
   __syncthreads();
 
-  // ---- the wave's own complex lines
-  cx<double>* L = buf + wave * LPW * G::LSZ;
-  if constexpr (ADJ) {
-    for (int e = lane; e < LPW * CE; e += 64) L[(e % LPW) * G::LSZ + G::pos(n + e / LPW)] = {0.0, 0.0};
-  } else {
-    // extension values (Sec. 4.3 steps 1-4 as one linear map of the 2d
-    // matching values): job (row p, line l)
-    for (int e = lane; e < LPW * CE; e += 64) {
-      const int l = e % LPW, p = e / LPW;
-      if (e >= 64) row.load(D, dd, p);
-      L[l * G::LSZ + G::pos(n + p)] = row.apply(D, dd, L + l * G::LSZ);
+  if (active) {
+    // ---- the wave's own complex lines
+    cx<double>* L = buf + wave * LPW * G::LSZ;
+    if constexpr (ADJ) {
+      for (int e = lane; e < LPW * CE; e += 64) L[(e % LPW) * G::LSZ + G::pos(n + e / LPW)] = {0.0, 0.0};
+    } else {
+      // extension values (Sec. 4.3 steps 1-4 as one linear map of the 2d
+      // matching values): job (row p, line l)
+      for (int e = lane; e < LPW * CE; e += 64) {
+        const int l = e % LPW, p = e / LPW;
+        if (e >= 64) row.load(D, dd, p);
+        L[l * G::LSZ + G::pos(n + p)] = row.apply(D, dd, L + l * G::LSZ);
+      }
     }
-  }
-  wave_order();
-  stage_a<G, -1>(L, lane, tw);
-  wave_order();
-  if constexpr (G::THREE) {
-    stage_b<G, -1>(L, lane, tw);
     wave_order();
-  }
-  stage_c<G>(L, lane, D.mu, D.coef + s0 + wave * LPW);
-  wave_order();
-  if constexpr (G::THREE) {
-    stage_b<G, 1>(L, lane, tw);
+    stage_a<G, -1>(L, lane, tw);
     wave_order();
-  }
-  // fold of the extension region onto the 2d matching points (transpose of the
-  // continuation): quad c sums column c over the extension rows.  From 128 to
-  // 600 points its first 8 coefficients are read before the last stage (N = 540:
-  // 437 us against 451, N = 160: 8.9 against 9.3; N = 90 and 1080 lose 4 and 1 %).
-  const int c = lane >> 2, part = lane & 3;
-  const bool on = c < 2 * dd;
-  constexpr int kFold = N >= 128 && N <= 600 ? 8 : 0;
-  double mf[kFold + 1];
-  if constexpr (ADJ) {
+    if constexpr (G::THREE) {
+      stage_b<G, -1>(L, lane, tw);
+      wave_order();
+    }
+    stage_c<G>(L, lane, D.mu, D.coef + s0 + wave * LPW);
+    wave_order();
+    if constexpr (G::THREE) {
+      stage_b<G, 1>(L, lane, tw);
+      wave_order();
+    }
+    // fold of the extension region onto the 2d matching points (transpose of the
+    // continuation): quad c sums column c over the extension rows.  From 128 to
+    // 600 points its first 8 coefficients are read before the last stage (N = 540:
+    // 437 us against 451, N = 160: 8.9 against 9.3; N = 90 and 1080 lose 4 and 1 %).
+    const int c = lane >> 2, part = lane & 3;
+    const bool on = c < 2 * dd;
+    constexpr int kFold = N >= 128 && N <= 600 ? 8 : 0;
+    double mf[kFold + 1];
+    if constexpr (ADJ) {
 #pragma unroll
-    for (int j = 0; j < kFold; ++j) mf[j] = D.Mx[min(part + 4 * j, CE - 1) * 2 * dd + min(c, 2 * dd - 1)];
-  }
-  stage_a<G, 1>(L, lane, tw);
-  wave_order();
-  if constexpr (ADJ) {
-    double sr[LPW] = {}, si[LPW] = {};
-    auto add = [&](int p, double mv) {
-      const cx<double>* y = L + G::pos(n + p);
+      for (int j = 0; j < kFold; ++j) mf[j] = D.Mx[min(part + 4 * j, CE - 1) * 2 * dd + min(c, 2 * dd - 1)];
+    }
+    stage_a<G, 1>(L, lane, tw);
+    wave_order();
+    if constexpr (ADJ) {
+      double sr[LPW] = {}, si[LPW] = {};
+      auto add = [&](int p, double mv) {
+        const cx<double>* y = L + G::pos(n + p);
+#pragma unroll
+        for (int l = 0; l < LPW; ++l) {
+          sr[l] += mv * y[l * G::LSZ].re;
+          si[l] += mv * y[l * G::LSZ].im;
+        }
+      };
+      if (on) {
+#pragma unroll
+        for (int j = 0; j < kFold; ++j)
+          if (part + 4 * j < CE) add(part + 4 * j, mf[j]);
+        for (int p = part + 4 * kFold; p < CE; p += 4) add(p, D.Mx[p * 2 * dd + c]);
+      }
+      cx<double>* q = L + (on ? G::pos(c < dd ? n - dd + c : 2 * dd - 1 - c) : 0);
 #pragma unroll
       for (int l = 0; l < LPW; ++l) {
-        sr[l] += mv * y[l * G::LSZ].re;
-        si[l] += mv * y[l * G::LSZ].im;
-      }
-    };
-    if (on) {
-#pragma unroll
-      for (int j = 0; j < kFold; ++j)
-        if (part + 4 * j < CE) add(part + 4 * j, mf[j]);
-      for (int p = part + 4 * kFold; p < CE; p += 4) add(p, D.Mx[p * 2 * dd + c]);
-    }
-    cx<double>* q = L + (on ? G::pos(c < dd ? n - dd + c : 2 * dd - 1 - c) : 0);
-#pragma unroll
-    for (int l = 0; l < LPW; ++l) {
-      const double fr = quad_sum(sr[l]), fi = quad_sum(si[l]);
-      if (on && part == 0) {
-        q[l * G::LSZ].re += fr;
-        q[l * G::LSZ].im += fi;
+        const double fr = quad_sum(sr[l]), fi = quad_sum(si[l]);
+        if (on && part == 0) {
+          q[l * G::LSZ].re += fr;
+          q[l * G::LSZ].im += fi;
+        }
       }
     }
   }
   __syncthreads();
 
-  if (it && !has1) return;
+  if (!active || (it && !has1)) return;
   const uint32_t lout = (it ? ls : 0u) + 16u * pc;
   char* out = reinterpret_cast<char*>(dout + base);
   const double* src = bufd + 2 * (pc * SL * G::LSZ) + it;
@@ -591,7 +598,7 @@ __global__ __launch_bounds__((Geo<N1, M>::NTH)) void lines4_kernel(Lines4Args<T>
   const int dirn = second ? 1 - a.first : a.first;
   const int line0 = 2 * (second ? u - a.units_first : u);
   if (line0 >= a.dir[dirn].nlines) return;
-  lines4_unit<T, ADJ, N1, M>(a, a.dir[dirn], a.out[dirn], line0, smem_raw);
+  lines4_unit<T, ADJ, N1, M>(a, a.dir[dirn], a.out[dirn], line0, smem_raw, true);
 }
 
 constexpr size_t kLines4MaxLds = 160 * 1024;

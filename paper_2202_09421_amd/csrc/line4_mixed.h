@@ -6,7 +6,7 @@
 // us, two launches and one (FP64): 25 x 21 x 8 7.6 / 9.2 and 4.3 / 5.1,
 // 60 x 40 x 16 8.3 / 10.2 and 4.6 / 5.4, 120 x 80 x 32 10.9 / 12.2 and
 // 6.8 / 7.1, 200 x 150 x 32 with two sources 21.5 / 22.3 and 17.3 / 16.6.  It
-// needs the registers of its largest length (172, two to three waves per SIMD)
+// needs the registers of its largest length (160, three waves per SIMD)
 // and the waves of the longer line, so larger grids keep two launches; and with
 // the lengths up to 600 in it, grids of those got slower (301 x 190 x 20, two
 // sources: 25.9 / 29.2 and 32.1 / 37.0).
@@ -60,15 +60,11 @@ __global__ __launch_bounds__(256) void lines4_mixed_kernel(Lines4Args<T> a) {
   T* dout = y ? a.out[1] : a.out[0];
   const int line0 = 2 * (second ? u - a.units_first : u);
   if (line0 >= D.nlines) return;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   switch (D.Np) {
-#define RTE_CASE(n, n1, m)                                              \
-  case n:                                                               \
-    if ((int)threadIdx.x < Geo<n1, m>::NTH) {                           \
-      lines4_unit<T, ADJ, n1, m>(a, D, dout, line0, smem_raw);          \
-    } else { /* the waves beyond this length's: its two barriers */     \
-      __syncthreads();                                                  \
-      __syncthreads();                                                  \
-    }                                                                   \
+#define RTE_CASE(n, n1, m)                                                                      \
+  case n:                                                                                       \
+    lines4_unit<T, ADJ, n1, m>(a, D, dout, line0, smem_raw, wave < Geo<n1, m>::NW);             \
     break;
     RTE_MIXED_SIZES(RTE_CASE)
 #undef RTE_CASE
