@@ -86,32 +86,7 @@ void line4_orders(int Np, std::vector<int>& mu, std::vector<int>& tw) {
   int n1 = 0, m = 0;
   mu.clear();
   tw.clear();
-  if (!fourstep_split(Np, &n1, &m)) return;
-  const int n2 = inner_n2(n1, m), n3 = m / n2;
-  const bool three = n3 > 1, pf1 = gcd_c(n1, m) == 1, pf2 = three && gcd_c(n2, n3) == 1;
-  const int last = three ? n3 : n2, jobs = Np / last;
-  mu.assign(Np, 0);
-  for (int i = 0; i < last; ++i)
-    for (int r = 0; r < jobs; ++r) {
-      const int k1 = three ? r / n2 : r, k2 = three ? r % n2 : 0;
-      const int km = !three ? i : (pf2 ? (n3 * k2 + n2 * i) % m : k2 + n2 * i);
-      mu[i * jobs + r] = pf1 ? (m * k1 + n1 * km) % Np : k1 + n1 * km;
-    }
-  // stage-A job j holds the block index jm with (jm mod n2, jm mod n3) = (j / n3, j % n3)
-  // in a coprime inner split, else jm = j
-  if (!pf1)
-    for (int p = 0; p < tw_powers(n1); ++p)
-      for (int j = 0; j < m; ++j) {
-        int jm = j;
-        if (pf2) {
-          jm = j % n3;
-          while (jm % n2 != j / n3) jm += n3;
-        }
-        tw.push_back((int)(((int64_t)jm << p) % Np));
-      }
-  if (three && !pf2)
-    for (int p = 0; p < tw_powers(n2); ++p)
-      for (int b = 0; b < n3; ++b) tw.push_back((int)(((int64_t)n1 * b << p) % Np));
+  if (fourstep_split(Np, &n1, &m)) split_orders(n1, m, mu, tw);
 }
 
 template <typename T, bool ADJ>
