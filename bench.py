@@ -757,7 +757,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--schedule", default=None, metavar="JSON",
-                    help='fixed launch schedule instead of autotuning, e.g. \'{"line_units_per_wave": 1, "line_waves_per_unit": 2}\'')
+                    help='fixed launch schedule instead of autotuning, e.g. \'{"node_tiles_per_block": 2}\'')
     ap.add_argument("--tune-cache", default=None, metavar="JSON",
                     help="autotuner cache file (reuse one tuned schedule across runs, e.g. profiler passes)")
     ap.add_argument("--uneven-scale", type=float, default=0.0,

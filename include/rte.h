@@ -175,7 +175,11 @@ int rte_forward_noalloc(rte_plan* plan, const void* mu_a, const void* mu_s, doub
  * rte_plan_autotune, rte_plan_time_kernels), or `workspace` is not the buffer
  * the saving call (rte_forward, rte_gradient, rte_gradient_continuous, a
  * batch gradient) used.  The medium must be the one of that call (not
- * checked).                                                                */
+ * checked).  Under stream capture every launch of the recorded call gives the
+ * adjoint of the forward that the workspace then holds.  A plan that has had a
+ * call recorded replays the last checkpoint segment, and with several chunks
+ * recomputes every chunk's forward, in each later adjoint; a plan that is only
+ * called eagerly leaves out what the workspace still holds.                */
 int rte_adjoint(rte_plan* plan, const void* mu_a, const void* mu_s, const double* G_bar,
                 double* dmu_a, double* dmu_s, void* workspace, int64_t workspace_bytes, void* stream);
 
@@ -349,11 +353,12 @@ int rte_plan_get_schedule(const rte_plan* plan, rte_schedule* out);
  * recorded graph is dropped (the next graph-mode call re-records).      */
 int rte_plan_set_schedule(rte_plan* plan, const rte_schedule* sched);
 
-/* Autotuner: times every admissible schedule of the four per-step kernel
- * classes on this plan's shapes (a few launches each, on `stream`, with
- * HIP events; the call synchronizes the stream), keeps the fastest choice
- * per class and stores it in the plan; `chosen` (host, may be NULL)
- * receives it.  Uses the gradient workspace (>= rte_workspace_bytes(plan,
+/* Autotuner: times the node passes with every admissible
+ * node_tiles_per_block on this plan's shapes (a few launches each, on `stream`,
+ * with HIP events; the call synchronizes the stream), keeps the fastest and
+ * stores it in the plan; `chosen` (host, may be NULL) receives the schedule.
+ * line_generic is set where no direction has a split line kernel and cleared
+ * elsewhere; the fields that select nothing keep their values.  Uses the gradient workspace (>= rte_workspace_bytes(plan,
  * 1)) as scratch: any saved forward is invalidated.  mu_a, mu_s as in
  * rte_forward.  Not for use under stream capture.                         */
 int rte_plan_autotune(rte_plan* plan, const void* mu_a, const void* mu_s, void* workspace,

@@ -19,9 +19,13 @@ constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
 // First factor N2 of the second factor m of a split n1 x m (m / N2 = N3; m
 // itself: one stage).  The splits of all lengths are the fastest of those with
 // the lowest instruction and LDS counts, forward plus transposed pass on an
-// (N - 25)-node square grid with 32 ordinates.  Three stages from 288 on: two
-// would need radices up to 32 (over 200 registers, two waves per SIMD) and
-// fill the lanes worse (20 x 27 at N = 540: 27 and 20 jobs a line for 64 lanes).
+// (N - 25)-node square grid with 32 ordinates.  That is three stages from 270
+// on but for five lengths: with two, most need radices up to 32 (over 200
+// registers, two waves per SIMD) and fill the lanes worse (20 x 27 at N = 540:
+// 27 and 20 jobs a line for 64 lanes).  375 = 15 x 25, 576 = 24 x 24, 625 = 25 x
+// 25, 729 = 27 x 27 and 800 = 32 x 25 measured faster in two all the same, and
+// twelve shorter lengths (48, 64, 75, 90, 96, 100, 125, 128, 162, 216, 243, 250)
+// in three.
 constexpr int inner_n2(int n1, int m) {
   switch (n1 * m) {
     case 216: case 675: case 810: return 3;
@@ -45,7 +49,7 @@ constexpr int inner_n2(int n1, int m) {
 // x 32 forward pass).  Long lines: one per wave, whose smaller radices leave
 // four waves per SIMD (N = 288: 20.1 us against 21.6 / 26.7 us with two / four,
 // 257 x 257 x 32; N = 540: 93 us against 102 / 146 us, 513 x 513 x 64).  In
-// between, and where the factors are odd primes, whichever measured faster.
+// between, and at the five long lengths of two stages, whichever measured faster.
 constexpr int lines_per_wave(int n1, int m) {
   const int N = n1 * m;
   switch (N) {

@@ -730,10 +730,11 @@ struct Layout {
   int64_t states, ckpts, work_u, lring, tx, ty, vring, atx, aty, w, flux, ga, gb, gbar, scratch, total;
 };
 
-// Forward: lring[3], tx, ty.  Adjoint: vring[4], the carries w, atx, aty.  With every state kept no forward step runs during the
-// adjoint, so vring[0..2] alias the L ring and atx aliases ty; with
-// checkpoints the segment replays need the forward arrays while the adjoint
-// ring and carries are live, so those are separate.
+// Forward: lring[3], tx, ty.  Adjoint: vring[4], the carries w, atx, aty.
+// With every state kept no forward step runs during the adjoint, so vring[0..2]
+// alias the L ring and atx aliases ty; with checkpoints the segment replays need
+// the forward arrays while the adjoint ring and carries are live, so those are
+// separate.
 static Layout layout(const Plan& p, bool adj) {
   const int64_t S = state_stride_bytes(p);
   const bool ck = p.ckpt_every > 0;

@@ -15,7 +15,7 @@ constexpr int kGroup = 4;        // ordinate slots per storage group (one reflec
 constexpr int kMaxPasses = 12;   // FFT passes (radices 2,3,4,5)
 constexpr int kMaxFcD = 8;       // matching points supported
 // state arrays (one chunk) above this size are streamed with the
-// non-temporal hint: a node pass then moves 8-10 such arrays, well beyond
+// non-temporal hint: a node pass then moves 8 or 9 such arrays, well beyond
 // the 256 MiB memory-side cache that holds smaller plans' arrays between
 // launches
 constexpr int64_t kStreamNtBytes = int64_t(64) << 20;
